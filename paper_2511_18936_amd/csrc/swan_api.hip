@@ -316,7 +316,7 @@ swan_status compress_prep(const swan_cache* c, const int32_t* seq_len_host,
   a.n_pages_cap = swan::pages_for(c->sparse_capacity);
   a.n_new = n_new;
   a.max_evict = max_evict;
-  a.prefill_groups = swan::prefill_groups(n_new, 0);
+  a.prefill_groups = 0;
   a.dtype = c->dtype;
   a.stream = (hipStream_t)stream;
   return SWAN_OK;

@@ -118,7 +118,7 @@ struct CompressLaunch {
   void* v_ring;
   int B, Hkv, bb, n_pages_cap, n_new;  // n_new: token stride of k_new / v_new
   int max_evict;  // largest per-sequence eviction count
-  int prefill_groups;  // waves per (sequence, head, role) of the prefill kernel
+  int prefill_groups;  // set by launch_prefill: workgroups per (sequence, head, role)
   int dtype;
   SeqTab tab;     // len = tokens cached before the call
   hipStream_t stream;
@@ -132,9 +132,8 @@ struct CompressLaunch {
 };
 constexpr int kStepQG = 8;
 hipError_t launch_compress(const CompressLaunch& a);
-// prefill path (fp16, many tokens): float64 MFMA rotation + lane-per-token top-k
+// prefill path (fp16, many tokens): int8 MFMA rotation, two lanes per token's top-k
 constexpr int kPrefillMinTokens = 64;
-int prefill_groups(int max_new_tokens, int min_len_old);
 hipError_t launch_prefill(const CompressLaunch& a);
 
 // run-time change of k: one launch per role, over the role's page arrays
