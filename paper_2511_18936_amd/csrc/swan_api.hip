@@ -1,4 +1,4 @@
-// Host side of the C ABI declared in include/swan.h: argument validation
+// Host side of the C ABI declared in include/swan.h and swan_layer.h: argument validation
 // (always before anything is enqueued), workspace sizing, split planning and
 // kernel launches.  No allocation, no host arithmetic on the data path.
 #include <math.h>
@@ -12,6 +12,7 @@
 
 #include "swan.h"
 #include "swan_internal.h"
+#include "swan_layer.h"
 
 // ---------------------------------------------------------------------------
 // Scratch of swan_decode_attention_noalloc: the decode workspace (q_hat, then
@@ -454,35 +455,61 @@ swan_status swan_calibrate_workspace_bytes(int32_t d, size_t* bytes) {
 swan_status swan_calibrate_rotation(const float* rows, int64_t n_rows, int32_t d, float* P_out,
                                     float* sigma_out, void* workspace, size_t workspace_bytes,
                                     void* stream) {
+  return swan_calibrate_rotations(rows, 1, &n_rows, d, P_out, sigma_out, workspace,
+                                  workspace_bytes, stream);
+}
+
+swan_status swan_calibrate_rotations(const float* rows, int32_t count,
+                                     const int64_t* n_rows_host, int32_t d, float* P_out,
+                                     float* sigma_out, void* workspace, size_t workspace_bytes,
+                                     void* stream) {
   if (d != SWAN_HEAD_DIM)
     return fail(SWAN_ERR_UNSUPPORTED, "d %d: the GPU path supports %d only", d, SWAN_HEAD_DIM);
   if (!rows || !P_out) return fail(SWAN_ERR_INVALID_ARG, "rows / P_out is NULL");
-  if (n_rows < 1) return fail(SWAN_ERR_INVALID_ARG, "n_rows %lld < 1", (long long)n_rows);
-  if (!workspace || workspace_bytes < swan::kCalibWorkspace)
-    return fail(SWAN_ERR_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes,
-                swan::kCalibWorkspace);
+  if (count < 1 || !n_rows_host)
+    return fail(SWAN_ERR_INVALID_ARG, "count %d < 1, or n_rows_host is NULL", count);
+  for (int32_t p = 0; p < count; ++p)
+    if (n_rows_host[p] < 1 || n_rows_host[p] > INT64_MAX / 4096)
+      return fail(SWAN_ERR_INVALID_ARG, "n_rows %lld (problem %d) < 1 or too large",
+                  (long long)n_rows_host[p], p);
+  const size_t need = swan::kCalibWorkspace * (size_t)count;
+  if (!workspace || workspace_bytes < need)
+    return fail(SWAN_ERR_WORKSPACE, "workspace of %zu bytes, need %zu", workspace_bytes, need);
   if (((uintptr_t)workspace & 15) != 0)
     return fail(SWAN_ERR_INVALID_ARG, "workspace must be 16-byte aligned");
-  char* ws = (char*)workspace;
+  constexpr size_t kMat = (size_t)swan::kD * swan::kD;
   swan::CalibLaunch a;
   a.rows = rows;
-  a.n_rows = n_rows;
-  a.P_out = P_out;
-  a.sigma_out = sigma_out;
-  a.gram = (double*)ws;
-  a.vecs = (double*)(ws + sizeof(double) * swan::kD * swan::kD);
-  a.status = (int32_t*)(ws + 2 * sizeof(double) * swan::kD * swan::kD);
   a.stream = (hipStream_t)stream;
-  hipError_t e = swan::launch_calibrate(a);
-  if (e != hipSuccess) return hip_status(e, "calibrate launch");
-  int32_t st_host[2] = {0, 0};
-  e = hipMemcpyAsync(st_host, a.status, sizeof(st_host), hipMemcpyDeviceToHost, a.stream);
-  if (e != hipSuccess) return hip_status(e, "calibrate status copy");
-  e = hipStreamSynchronize(a.stream);
-  if (e != hipSuccess) return hip_status(e, "calibrate synchronize");
-  if (!st_host[0])
-    return fail(SWAN_ERR_NO_CONVERGENCE, "Jacobi eigensolver did not converge in %d sweeps",
-                st_host[1]);
+  int64_t row = 0;
+  for (int32_t p0 = 0; p0 < count; p0 += swan::kMaxCalib) {
+    a.count = count - p0 < swan::kMaxCalib ? count - p0 : swan::kMaxCalib;
+    for (int p = 0; p < a.count; ++p) {
+      a.row0[p] = row;
+      a.n_rows[p] = n_rows_host[p0 + p];
+      row += a.n_rows[p];
+    }
+    a.P_out = P_out + p0 * kMat;
+    a.sigma_out = sigma_out ? sigma_out + (size_t)p0 * swan::kD : nullptr;
+    a.gram = (double*)((char*)workspace + swan::kCalibWorkspace * (size_t)p0);
+    a.vecs = a.gram + a.count * kMat;
+    a.part = a.vecs + a.count * kMat;
+    a.lam = a.part + a.count * swan::kCalibPart;
+    a.status = (int32_t*)(a.lam + (size_t)a.count * swan::kD);
+    hipError_t e = swan::launch_calibrate(a);
+    if (e != hipSuccess) return hip_status(e, "calibrate launch");
+    int32_t st_host[2 * swan::kMaxCalib] = {};  // each problem's (converged, sweeps)
+    e = hipMemcpyAsync(st_host, a.status, 2 * a.count * sizeof(int32_t), hipMemcpyDeviceToHost,
+                       a.stream);
+    if (e != hipSuccess) return hip_status(e, "calibrate status copy");
+    e = hipStreamSynchronize(a.stream);
+    if (e != hipSuccess) return hip_status(e, "calibrate synchronize");
+    for (int p = 0; p < a.count; ++p)
+      if (!st_host[2 * p])
+        return fail(SWAN_ERR_NO_CONVERGENCE,
+                    "Jacobi eigensolver did not converge in %d sweeps (problem %d)",
+                    st_host[2 * p + 1], p0 + p);
+  }
   return ok();
 }
 

@@ -164,18 +164,29 @@ struct RopeLaunch {
 };
 hipError_t launch_rope(const RopeLaunch& a);
 
+constexpr int kMaxCalib = 64;  // problems per launch
 struct CalibLaunch {
-  const float* rows;
-  int64_t n_rows;
-  float* P_out;
-  float* sigma_out;
-  double* gram;    // [128][128]
-  double* vecs;    // [128][128]
-  int32_t* status; // [4]: converged flag, sweeps
+  const float* rows;           // the problems' rows, 128 floats each
+  int64_t row0[kMaxCalib];     // first row of each problem
+  int64_t n_rows[kMaxCalib];
+  int count;                   // problems solved side by side
+  float* P_out;       // [count][128][128]
+  float* sigma_out;   // [count][128] or null
+  double* gram;       // [count][128][128]
+  double* vecs;       // [count][128][128]
+  double* lam;        // [count][128]
+  double* part;       // [count][kGramChunks][3][64][64]; then the Jacobi rotations
+  int32_t* status;    // [count][2]: converged, sweeps
   hipStream_t stream;
 };
 hipError_t launch_calibrate(const CalibLaunch& a);
-constexpr size_t kCalibWorkspace = 2 * sizeof(double) * kD * kD + 256;
 constexpr int kJacobiMaxSweeps = 40;
+constexpr int kGramChunks = 32;
+// workspace per problem, in doubles: gram, vecs, lam, partials, status
+constexpr size_t kCalibPart = (size_t)kGramChunks * 3 * 64 * 64;
+constexpr size_t kCalibWorkspace = sizeof(double) * (2 * kD * kD + kD + kCalibPart + 32);
+static_assert(kCalibPart * sizeof(double) >=
+                  (size_t)kJacobiMaxSweeps * (kD - 1) * (kD / 2) * sizeof(float),
+              "the rotations take the partials' place");
 
 }  // namespace swan

@@ -35,7 +35,7 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     (query heads jG .. jG + G - 1) the joint matrices are stacked in device
     memory as float32, S_QK = [Q_grouped^(j); K^(j)] and S_VO = [V^(j); W_O^(h)^T
     for the group's heads], W_O^(h) being rows 128 h .. 128 h + 127 of W_o, and
-    swan_calibrate_rotation writes their right singular matrices to P_qk_out[j]
+    swan_calibrate_rotations writes their right singular matrices to P_qk_out[j]
     and P_vo_out[j] ([N_kv][128][128] float32)."""
     import torch
 
@@ -49,14 +49,27 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     G = n_q // n_kv_heads
     hidden = W_o.shape[1]
     q_grouped = q.reshape(n_kv_heads, n * G, d)
-    blocks = W_o.reshape(n_q, d, hidden)  # W_O^(h)
-    ws = torch.empty(swan.calibrate_workspace_bytes(d), dtype=torch.uint8, device=q.device)
-    for j in range(n_kv_heads):
-        s_qk = torch.cat([q_grouped[j], k[j]], dim=0).float().contiguous()
-        swan.calibrate_rotation(s_qk, P_qk_out[j], workspace=ws, stream=stream)
-        wo_t = blocks[j * G:(j + 1) * G].transpose(1, 2).reshape(G * hidden, d)
-        s_vo = torch.cat([v[j], wo_t], dim=0).float().contiguous()
-        swan.calibrate_rotation(s_vo, P_vo_out[j], workspace=ws, stream=stream)
+    # every joint matrix in one array, S_QK of the heads, then S_VO, solved side by side
+    rows_qk, rows_vo = n * (G + 1), n + G * hidden
+    s = torch.empty((n_kv_heads * (rows_qk + rows_vo), d), dtype=torch.float32, device=q.device)
+    s_qk = s[:n_kv_heads * rows_qk].view(n_kv_heads, rows_qk, d)
+    s_qk[:, :n * G] = q_grouped
+    s_qk[:, n * G:] = k
+    s_vo = s[n_kv_heads * rows_qk:].view(n_kv_heads, rows_vo, d)
+    s_vo[:, :n] = v
+    wo_t = W_o.reshape(n_kv_heads, G, d, hidden).transpose(2, 3)  # W_O^(h) transposed
+    s_vo[:, n:].unflatten(1, (G, hidden)).copy_(wo_t)
+    P = torch.empty((2 * n_kv_heads, d, d), dtype=torch.float32, device=q.device)
+    if stream is not None:  # the stacking above ran on the current stream
+        stream.wait_stream(torch.cuda.current_stream(q.device))
+    swan.calibrate_rotations(s, [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads, P,
+                             stream=stream)
+    for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
+        if isinstance(out, torch.Tensor):
+            out.copy_(got)
+        else:  # a list of matrices
+            for j in range(n_kv_heads):
+                out[j].copy_(got[j])
 
 
 class SwanAttentionLayer:

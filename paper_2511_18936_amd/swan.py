@@ -1,4 +1,5 @@
-"""ctypes binding of libswan (include/swan.h), plus a small cache holder.
+"""ctypes binding of libswan (include/swan.h, include/swan_layer.h), plus a small cache
+holder.
 
 Argument marshalling only: every step of the path runs in the library's HIP
 kernels.  PyTorch provides device memory and the current stream.  If the
@@ -91,6 +92,7 @@ def _load() -> ctypes.CDLL:
         "swan_cache_bytes": [pdesc, pi32, pi32, psz, psz, psz],
         "swan_calibrate_workspace_bytes": [i32, psz],
         "swan_calibrate_rotation": [vp, i64, i32, vp, vp, vp, sz, vp],
+        "swan_calibrate_rotations": [vp, i32, ctypes.POINTER(i64), i32, vp, vp, vp, sz, vp],
         "swan_compress_append": [pdesc, pi32, pi32, pi32, vp, vp, i32, pi32, vp, vp, vp],
         "swan_decode_workspace_bytes": [pdesc, pi32, pi32, pi32, psz],
         "swan_decode_attention": [pdesc, pi32, pi32, pi32, vp, vp, vp, ctypes.c_float, vp, vp, sz,
@@ -246,6 +248,27 @@ def calibrate_rotation(rows, P_out, sigma_out=None, workspace=None, stream=None)
                                 device=rows.device)
     _check(_lib.swan_calibrate_rotation(_ptr(rows), n, d, _ptr(P_out), _ptr(sigma_out),
                                         _ptr(workspace), workspace.numel(), _stream(stream)))
+
+
+def calibrate_rotations(rows, n_rows: Sequence[int], P_out, sigma_out=None, workspace=None,
+                        stream=None) -> None:
+    """calibrate_rotation of several problems at once: `rows` ([sum(n_rows)][d] float32,
+    cuda) holds n_rows[i] rows of problem i, one problem after another; into P_out
+    ([len(n_rows)][d][d] float32)."""
+    import torch
+
+    count, d = len(n_rows), rows.shape[1]
+    _tensor(rows, "rows", torch.float32, (sum(n_rows), d))
+    _tensor(P_out, "P_out", torch.float32, (count, d, d))
+    if sigma_out is not None:
+        _tensor(sigma_out, "sigma_out", torch.float32, (count, d))
+    _on_gpu(rows=rows, P_out=P_out, sigma_out=sigma_out)
+    if workspace is None:
+        workspace = torch.empty(count * calibrate_workspace_bytes(d), dtype=torch.uint8,
+                                device=rows.device)
+    _check(_lib.swan_calibrate_rotations(_ptr(rows), count, (ctypes.c_int64 * count)(*n_rows), d,
+                                         _ptr(P_out), _ptr(sigma_out), _ptr(workspace),
+                                         workspace.numel(), _stream(stream, rows.get_device())))
 
 
 def compress_append(desc: CacheDesc, seq_len: Sequence[int], k_active: Sequence[int], k_new,

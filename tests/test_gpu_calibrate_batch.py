@@ -1,0 +1,43 @@
+"""Rotations of several problems in one call: each the same as from a call of its own
+(bit for bit), at the edges of the row chunks, few rows (rank below 128), a matrix of
+zeros, repeated singular values and scales near the ends of float32."""
+import numpy as np
+import pytest
+
+import swan_inputs as si
+from oracle import swan_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+def _problems(torch, device):
+    rng = si.rng_for(31)
+    R = si.haar_orthogonal(rng, 128)
+    S = [si.lowrank_rows(rng, n, R) for n in (1, 15, 16, 17, 127, 128, 512, 513, 4099)]
+    S.append(np.zeros((40, 128)))
+    S.append(np.concatenate([np.eye(128)] * 3))             # all singular values equal
+    S.append(si.lowrank_rows(rng, 300, R) * 2.0 ** -60)
+    S.append(si.lowrank_rows(rng, 300, R) * 2.0 ** 60)
+    S += [rng.standard_normal((200, 128)) for _ in range(66 - len(S))]  # more than one launch
+    return [torch.tensor(np.ascontiguousarray(x, dtype=np.float32), device=device) for x in S]
+
+
+def test_batch_equals_single_calls(gpu_device, swan_mod, torch_mod):
+    torch = torch_mod
+    S = _problems(torch, gpu_device)
+    P = torch.empty((len(S), 128, 128), device=gpu_device)
+    sig = torch.empty((len(S), 128), device=gpu_device)
+    swan_mod.calibrate_rotations(torch.cat(S), [x.shape[0] for x in S], P, sig)
+    for i, x in enumerate(S):
+        p1, s1 = torch.empty_like(P[i]), torch.empty_like(sig[i])
+        swan_mod.calibrate_rotation(x, p1, s1)
+        assert torch.equal(p1, P[i]) and torch.equal(s1, sig[i]), i
+        # orthogonal, and the singular values of x in descending order
+        p = p1.double().cpu().numpy()
+        assert np.max(np.abs(p.T @ p - np.eye(128))) < 1e-6
+        ref = O.calibrate(x.cpu().numpy())[1] if x.shape[0] >= 128 else None
+        got = s1.double().cpu().numpy()
+        assert np.all(np.diff(got) <= 0)
+        if ref is not None:
+            # float64 solve: 1e-15 of the largest eigenvalue, in sigma^2
+            assert np.max(np.abs(got - ref)) <= 1e-6 * ref[0] + 1e-30
