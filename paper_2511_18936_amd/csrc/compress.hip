@@ -1,17 +1,16 @@
 // Compress-append (Algorithm 1, the steps that project, append, evict and
 // prune).
 //
-// Several new tokens per sequence: two launches on the caller's stream, so
-// that every vector leaving the ring is read before a new token overwrites its
-// slot.  One new token (a decode step): one launch, step_kernel, which evicts
-// the slot's old vector before it writes the new one.
+// Several new tokens per sequence: every vector leaving the ring is read before
+// a new token overwrites its slot, by the same workgroup (short appends) or in
+// an earlier launch.  One new token (a decode step): one launch, step_kernel,
+// which evicts the slot's old vector before it writes the new one.
 //   evict_kernel   one wave per ring vector that leaves the buffer: top-k of
 //                  its stored values, packed into its page slot
-//   insert_kernel  one wave per group of kTPW new tokens of one (sequence, kv
-//                  head, role): rotation x . P accumulated in float64 and
-//                  rounded once to the storage type; tokens still inside the
-//                  buffer go to their ring slot, the others are pruned and
-//                  packed at once
+//   insert_kernel  one workgroup per (sequence, kv head, role) and some pages:
+//                  rotation x . P in float64 on MFMA, rounded once to the
+//                  storage type; tokens still inside the buffer go to their
+//                  ring slot, the others are pruned and packed at once
 //   step_kernel    a decode step: one workgroup of four waves per (sequence,
 //                  kv head, role), each wave a quarter of P's rows; the same
 //                  rounding, ring write or pruning, and the eviction.  In
@@ -30,8 +29,6 @@
 #include "swan_internal.h"
 
 namespace swan {
-
-constexpr int kTPW = 8;  // new tokens per insert wave (several new tokens per sequence)
 
 // Write the top-k of a 128-vector of stored values (lane holds elements 2l,
 // 2l+1) into page slot `slot` of the page at `page`, in page format F (the
@@ -135,82 +132,270 @@ __global__ __launch_bounds__(64) void evict_kernel(CompressLaunch a) {
   select_and_pack<F>(x0, x1, k, page, p % kPage, lane);
 }
 
-template <typename F, int TPW>
-__global__ __launch_bounds__(64) void insert_kernel(CompressLaunch a) {
+// ---------------------------------------------------------------------------
+// several new tokens
+// ---------------------------------------------------------------------------
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kInsWaves = 8;
+constexpr int kXStride = kD + 4;  // LDS row of one token's 128 float32 values (+ pad)
+constexpr int kIdxStride = kD + 8;  // LDS row of one token's kept dims (+ pad)
+
+// sum over the 8 lanes of a token, in every lane (lanes xor 1, 2, then the
+// mirror of the 8)
+__device__ __forceinline__ int sum8(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);   // quad_perm 1 0 3 2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // quad_perm 2 3 0 1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xF, 0xF, false);  // row_half_mirror
+  return v;
+}
+// sum over the lanes of the token below this one (sub: lane in the token)
+__device__ __forceinline__ int below8(int v, int sub) {
+  int y = v;
+  const int a = __builtin_amdgcn_update_dpp(0, y, 0x111, 0xF, 0xF, false);  // row_shr 1
+  y += sub >= 1 ? a : 0;
+  const int b = __builtin_amdgcn_update_dpp(0, y, 0x112, 0xF, 0xF, false);
+  y += sub >= 2 ? b : 0;
+  const int c = __builtin_amdgcn_update_dpp(0, y, 0x114, 0xF, 0xF, false);
+  y += sub >= 4 ? c : 0;
+  return y - v;
+}
+
+// Eight lanes per token, 16 dims each (lane sub: dims 16 sub ..): the token's k
+// kept pairs, ties to the lower dim, packed in ascending order into its LDS row
+// (values, over the row itself, which the lanes have read by then) and `idx`
+// (dims); entries k..kp-1 are the padding, value +0 at the lowest dims not kept.
+// Lanes with on == false write nothing.
+template <typename St>
+__device__ __forceinline__ void select_rows(typename St::Bits* row, uint8_t* idx, int k, int kp,
+                                            int sub, bool on) {
+  using Bits = typename St::Bits;
+  constexpr int W = (int)sizeof(Bits) * 16 / 4;  // this lane's words
+  uint32_t w[W];
+#pragma unroll
+  for (int c = 0; c < W / 4; ++c) {
+    const u32x4 v = *(const u32x4*)(row + 16 * sub + c * (16 / (int)sizeof(Bits)));
+    w[4 * c] = v.x;
+    w[4 * c + 1] = v.y;
+    w[4 * c + 2] = v.z;
+    w[4 * c + 3] = v.w;
+  }
+  // The k-th largest magnitude, from the top bit down, or as soon as a candidate
+  // has exactly k magnitudes at or above it, that candidate: the same k are kept.
+  // (The wave stops when its 8 tokens have: for float32 after about 20 of 31 bits.)
+  uint32_t thr = 0u;
+  bool open = true;
+#pragma unroll 1
+  for (int bit = St::kMagBits - 1; bit >= 0 && __ballot(open) != 0ull; --bit) {
+    const uint32_t cand = thr | (1u << bit);
+    int cnt = 0;
+#pragma unroll
+    for (int i = 0; i < W; ++i) {
+      if constexpr (sizeof(Bits) == 2)  // two magnitudes per word: bits 15 and 31 stay when >=
+        cnt += __popc((((w[i] & 0x7FFF7FFFu) | 0x80008000u) - cand * 0x10001u) & 0x80008000u);
+      else
+        cnt += (w[i] & 0x7FFFFFFFu) >= cand ? 1 : 0;
+    }
+    const int all = sum8(cnt);
+    thr = open && all >= k ? cand : thr;
+    open = open && all != k;
+  }
+  auto bits_of = [&](int i) -> uint32_t {
+    if constexpr (sizeof(Bits) == 2) return (w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
+    else return w[i];
+  };
+  uint32_t gt = 0u, eq = 0u;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const uint32_t m = St::mag((Bits)bits_of(i));
+    gt |= m > thr ? 1u << i : 0u;
+    eq |= m == thr ? 1u << i : 0u;
+  }
+  const int ngt = sum8(__popc(gt)), neq = __popc(eq);
+  int quota = k - ngt - below8(neq, sub);  // of this lane's ties, the lowest first
+  quota = quota < 0 ? 0 : quota > neq ? neq : quota;
+  while (__popc(eq) > quota) eq &= ~(0x80000000u >> __clz(eq));
+  const uint32_t kept = gt | eq;
+  int e = below8(__popc(kept), sub);
+  const int r0 = 16 * sub - e;  // dims not kept below this lane's
+  if (!on) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i)
+    if ((kept >> i) & 1u) {
+      row[e] = (Bits)bits_of(i);
+      idx[e] = (uint8_t)(16 * sub + i);
+      ++e;
+    }
+  if (kp > k) {  // uniform
+    uint32_t rest = ~kept & 0xFFFFu;
+    for (int r = r0; rest != 0u && r < kp - k; ++r) {
+      idx[k + r] = (uint8_t)(16 * sub + __builtin_ctz(rest));
+      rest &= rest - 1u;
+    }
+    if (sub < kp - k) row[k + sub] = 0;
+  }
+}
+
+// `blocks` blocks of `bt` positions per workgroup: 64 (pages), or, when no new
+// token is pruned (every sequence's fit its buffer), 16, 32 or 64.  evict: the
+// workgroup first prunes and packs the vectors that leave the buffer: all of its
+// unit's (it has all of the unit's blocks), or, when none of the new tokens is
+// pruned, those whose slots its own tokens take.  Wave w holds columns 16 w .. of P
+// in registers for all of the workgroup's blocks.  Per block: the tokens' rows to
+// LDS, x . P on v_mfma_f64_16x16x4 (32 per 16 tokens and 16 columns), the rounded
+// rows to LDS, then the dense rows to the ring and the kept pairs, packed in LDS,
+// to the page (a wave's store is 1 KiB contiguous).
+//
+// What bounds it: many tokens, the float64 MFMAs (64 cycles each; two workgroups
+// share a compute unit, one's selection under the other's MFMAs); few, the chain
+// of loads and barriers.
+template <typename F>
+__global__ __launch_bounds__(64 * kInsWaves) __attribute__((amdgpu_waves_per_eu(4)))
+void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict) {
   using T = typename Fmt<F>::Elem;
   using St = Store<T>;
-  __shared__ __attribute__((aligned(16))) double xs[kD][TPW];
-  const int lane = threadIdx.x;
-  const int ngroups = (a.n_new + TPW - 1) / TPW;
+  using Bits = typename St::Bits;
+  constexpr int VB = Fmt<F>::kValBytes, CB = Fmt<F>::kChunkBytes;
+  constexpr int EV = 16 / (int)sizeof(T);                     // elements per 16-byte load
+  constexpr int RS = kD + 16 / (int)sizeof(T);                // LDS row of stored values
+  __shared__ __attribute__((aligned(16))) float xs[kPage * kXStride];
+  __shared__ __attribute__((aligned(16))) Bits rows[kPage * RS];  // as stored
+  __shared__ __attribute__((aligned(16))) uint8_t idxs[kPage * kIdxStride];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 15, g = lane >> 4;
   int w = blockIdx.x;
-  const int grp = w % ngroups;
-  w /= ngroups;
+  const int grp = w % groups;
+  w /= groups;
   const int role = w & 1;
   w >>= 1;
   const int h = w % a.Hkv;
   const int b = w / a.Hkv;
-  const int t0 = grp * TPW;
   const int nnew = a.tab.nnew[b];
-  if (t0 >= nnew) return;
-  const int nt = (nnew - t0) < TPW ? (nnew - t0) : TPW;
-  const T* x = (const T*)(role ? a.v_new : a.k_new) +
-               (((int64_t)b * a.Hkv + h) * a.n_new + t0) * kD;
-  for (int t = 0; t < TPW; ++t) {
-    double v0 = 0.0, v1 = 0.0;
-    if (t < nt) {
-      v0 = (double)(float)x[(int64_t)t * kD + 2 * lane];
-      v1 = (double)(float)x[(int64_t)t * kD + 2 * lane + 1];
-    }
-    xs[2 * lane][t] = v0;
-    xs[2 * lane + 1][t] = v1;
-  }
-  __syncthreads();
-  double acc0[TPW], acc1[TPW];
+  if (nnew == 0) return;  // uniform
+  const int len_old = a.tab.len[b], len_new = len_old + nnew;
+  // no new token is pruned when all fit the buffer: blocks then begin anywhere
+  const bool fits = nnew <= a.bb;
+  const int org = fits ? len_old : len_old & ~(kPage - 1);
+  const int nblk = (len_new - org + bt - 1) / bt;
+  const int blk0 = grp * blocks, blk1 = blk0 + blocks < nblk ? blk0 + blocks : nblk;
+  if (blk0 >= blk1) return;  // uniform
+  const T* x = (const T*)(role ? a.v_new : a.k_new) + ((int64_t)b * a.Hkv + h) * a.n_new * kD;
   const float* Prole = role ? a.P_vo : a.P_qk;
-  if (!Prole) {  // values already in the rotated basis (P_VO absorbed into W_V)
+  // the k dims of an MFMA step in any order, the same for x and P: lane group g
+  // takes dims 32 g + s in step s, so that a lane's x are contiguous
+  float pr[32];
+  if (Prole) {
+    const float* P = Prole + (int64_t)h * kD * kD + (int64_t)(32 * g) * kD + 16 * wave + m;
 #pragma unroll
-    for (int t = 0; t < TPW; ++t) {
-      acc0[t] = xs[2 * lane][t];
-      acc1[t] = xs[2 * lane + 1][t];
-    }
-  } else {
-    const float2* P = (const float2*)(Prole + (int64_t)h * kD * kD) + lane;
-#pragma unroll
-    for (int t = 0; t < TPW; ++t) acc0[t] = acc1[t] = 0.0;
-    // 32 rows of P in flight per batch: the loads are the latency of this kernel
-#pragma unroll 32
-    for (int i = 0; i < kD; ++i) {
-      const float2 pr = P[i * (kD / 2)];
-      const double p0 = (double)pr.x, p1 = (double)pr.y;
-#pragma unroll
-      for (int t = 0; t < TPW; ++t) {
-        const double xv = xs[i][t];
-        acc0[t] = fma(xv, p0, acc0[t]);
-        acc1[t] = fma(xv, p1, acc1[t]);
-      }
-    }
+    for (int s = 0; s < 32; ++s) pr[s] = P[s * kD];
   }
-  const int len_old = a.tab.len[b];
-  const int len_new = len_old + nnew;
-  const int k = a.tab.kact[role][b];
-  const int64_t pbytes = page_bytes_of(Fmt<F>::kValBytes, k);
+  const int k = a.tab.kact[role][b], kp = kpad_of(k);
+  const int64_t pbytes = page_bytes_of(VB, k);
   char* pages = (char*)(role ? a.v_pages : a.k_pages) + a.tab.page_off[role][b] +
                 (int64_t)h * a.n_pages_cap * pbytes;
-  typename St::Bits* ring = (typename St::Bits*)(role ? a.v_ring : a.k_ring) +
-                            ((int64_t)b * a.Hkv + h) * a.bb * kD;
-#pragma unroll
-  for (int t = 0; t < TPW; ++t) {
-    if (t >= nt) break;
-    const typename St::Bits y0 = St::from_f64(acc0[t]);
-    const typename St::Bits y1 = St::from_f64(acc1[t]);
-    const int pos = len_old + t0 + t;
-    if (pos >= len_new - a.bb) {  // stays dense: ring slot pos % b
-      typename St::Bits* r = ring + (int64_t)(pos % a.bb) * kD;
-      r[2 * lane] = y0;
-      r[2 * lane + 1] = y1;
-    } else {  // pruned on arrival
-      select_and_pack<F>(y0, y1, k, pages + (int64_t)(pos / kPage) * pbytes, pos % kPage, lane);
+  Bits* ring = (Bits*)(role ? a.v_ring : a.k_ring) + ((int64_t)b * a.Hkv + h) * a.bb * kD;
+  if (evict) {
+    int p0 = evict_begin(len_old, a.bb), p1 = evict_end(len_old, nnew, a.bb);
+    if (fits) {
+      const int q0 = org + blk0 * bt - a.bb, q1 = org + blk1 * bt - a.bb;
+      p0 = p0 > q0 ? p0 : q0;
+      p1 = p1 < q1 ? p1 : q1;
     }
+    for (int p = p0 + wave; p < p1; p += kInsWaves) {
+      const Bits* old = ring + (int64_t)(p % a.bb) * kD;
+      const Bits o0 = old[2 * lane], o1 = old[2 * lane + 1];
+      select_and_pack<F>(o0, o1, k, pages + (int64_t)(p / kPage) * pbytes, p % kPage, lane);
+    }
+  }
+  const int first_dense = len_new - a.bb;  // positions from here on stay in the buffer
+  for (int blk = blk0; blk < blk1; ++blk) {
+    const int pos0 = org + blk * bt;
+    const int lo = len_old > pos0 ? len_old - pos0 : 0;          // the block's new tokens
+    const int hi = len_new - pos0 < bt ? len_new - pos0 : bt;
+    for (int v = tid; v < bt * kD / EV; v += 64 * kInsWaves) {
+      const int t = v / (kD / EV), c = v % (kD / EV);
+      if (t < (lo & ~15) || t >= ((hi + 15) & ~15)) continue;
+      u32x4 q = {0u, 0u, 0u, 0u};
+      if (t >= lo && t < hi) q = *(const u32x4*)(x + (int64_t)(pos0 + t - len_old) * kD + c * EV);
+      float4* dst = (float4*)(xs + t * kXStride + c * EV);
+      if constexpr (sizeof(T) == 2) {
+        dst[0] = make_float4(f16_bits_to_f32(q.x & 0xFFFFu), f16_bits_to_f32(q.x >> 16),
+                             f16_bits_to_f32(q.y & 0xFFFFu), f16_bits_to_f32(q.y >> 16));
+        dst[1] = make_float4(f16_bits_to_f32(q.z & 0xFFFFu), f16_bits_to_f32(q.z >> 16),
+                             f16_bits_to_f32(q.w & 0xFFFFu), f16_bits_to_f32(q.w >> 16));
+      } else {
+        dst[0] = make_float4(__uint_as_float(q.x), __uint_as_float(q.y), __uint_as_float(q.z),
+                             __uint_as_float(q.w));
+      }
+    }
+    __syncthreads();  // the rows; the first time also the evictions' ring reads
+    // 16 tokens at a time; result layout: register v of lane l is token 16 T + 4 v +
+    // l / 16, dim 16 wave + l % 16
+#pragma unroll 1
+    for (int T = lo / 16; T < (hi + 15) / 16; ++T) {
+      f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      if (Prole) {
+#pragma unroll
+        for (int s4 = 0; s4 < 8; ++s4) {
+          const float4 xv = *(const float4*)(xs + (16 * T + m) * kXStride + 32 * g + 4 * s4);
+          const float xe[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)xe[i], (double)pr[4 * s4 + i], acc,
+                                                       0, 0, 0);
+        }
+      } else {  // values already in the rotated basis (P_VO absorbed into W_V)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          acc[v] = (double)xs[(16 * T + 4 * v + g) * kXStride + 16 * wave + m];
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        Bits y;
+        if constexpr (sizeof(Bits) == 2) y = f64_to_f16_bits_fast(acc[v]);
+        else y = St::from_f64(acc[v]);
+        rows[(16 * T + 4 * v + g) * RS + 16 * wave + m] = y;
+      }
+    }
+    __syncthreads();
+    // dense tokens to the ring: slot pos % b
+    const int dlo = first_dense > pos0 + lo ? first_dense - pos0 : lo;
+    for (int v = tid + dlo * (kD / EV); v < hi * (kD / EV); v += 64 * kInsWaves) {
+      const int t = v / (kD / EV), c = v % (kD / EV);
+      *(u32x4*)(ring + (int64_t)((pos0 + t) % a.bb) * kD + c * EV) =
+          *(const u32x4*)(rows + t * RS + c * EV);
+    }
+    // the others pruned: slots [lo, plo) of the block's page
+    const int phi = first_dense - pos0 < hi ? first_dense - pos0 : hi;
+    if (phi > lo) {  // uniform
+      const int t = 8 * wave + (lane >> 3), sub = lane & 7;
+      if (8 * wave < phi && 8 * wave + 8 > lo) {
+        const bool on = t >= lo && t < phi;
+        select_rows<St>(rows + t * RS, idxs + t * kIdxStride, k, kp, sub, on);
+      }
+      __syncthreads();
+      char* page = pages + (int64_t)(pos0 / kPage) * pbytes;
+      if (lane >= lo && lane < phi) {
+        const char* row = (const char*)(rows + lane * RS);
+        for (int c = wave; c < kp * VB / CB; c += kInsWaves) {
+          const u32x4 v = *(const u32x4*)(row + 16 * c);
+          if constexpr (std::is_same<F, E4M3V>::value) {
+            uint32_t q[2] = {0u, 0u};
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+              q[i >> 2] |= f16_bits_to_e4m3((v[i >> 1] >> (16 * (i & 1))) & 0xFFFFu)
+                           << (8 * (i & 3));
+            *(u32x2*)(page + c * (kPage * CB) + lane * CB) = u32x2{q[0], q[1]};
+          } else {
+            *(u32x4*)(page + c * (kPage * CB) + lane * CB) = v;
+          }
+        }
+        char* ip = page + (int64_t)kPage * kp * VB;
+        for (int c = wave; c < kp / 8; c += kInsWaves)
+          *(u32x2*)(ip + c * 512 + lane * 8) = *(const u32x2*)(idxs + lane * kIdxStride + 8 * c);
+      }
+    }
+    __syncthreads();  // the rows have been read
   }
 }
 
@@ -366,16 +551,51 @@ static hipError_t launch_compress_t(const CompressLaunch& a) {
     }
     return hipGetLastError();
   }
-  if (a.max_evict > 0) {
+  bool fit = true;  // no new token is pruned
+  int longest = 0;
+  for (int b = 0; b < a.B; ++b) {
+    fit = fit && a.tab.nnew[b] <= a.bb;
+    longest = a.tab.nnew[b] > longest ? a.tab.nnew[b] : longest;
+  }
+  // Positions per block: where no new token is pruned, so many that two
+  // workgroups per compute unit share the tokens (8 sequences x 8 kv heads x 40
+  // tokens: 12.4 us with blocks of 16, 16.2 with blocks of 64).
+  int bt = kPage;
+  if (fit)
+    while (bt > 16 && (int64_t)units * ((longest + bt / 2 - 1) / (bt / 2)) <= 512) bt /= 2;
+  int most = 0;       // blocks of one unit
+  int64_t total = 0;  // blocks of all
+  for (int b = 0; b < a.B; ++b) {
+    const int org = a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
+    const int n = a.tab.nnew[b] ? (a.tab.len[b] + a.tab.nnew[b] - org + bt - 1) / bt : 0;
+    most = n > most ? n : most;
+    total += (int64_t)n * 2 * a.Hkv;
+  }
+  // Long appends of binary16 rows go to the prefill kernel: its rotation on int8
+  // MFMA has twice the rate of float64's, but a workgroup first makes P's digits
+  // and takes 256 tokens at a time.  Measured (one unit = a kv head's keys or
+  // values, us, insert / prefill): 16 units x 1024 tokens 19 / 32, 128 x 256 31 /
+  // 33, 128 x 1024 105 / 67; 1024 units x 64 tokens 73 / 98, x 256 198 / 123.
+  const bool prefill = a.n_new >= kPrefillMinTokens && total > kPrefillMinBlocks &&
+                       sizeof(typename Fmt<F>::Elem) == 2;
+  // Blocks per workgroup: P's columns are loaded once for all of them (~2 us), so
+  // many blocks go up to 8 to a workgroup, as long as the GPU keeps 4 rounds of
+  // two workgroups per compute unit.  Where the units alone fill it, a few blocks
+  // stay together, so that the eviction needs no launch of its own.
+  int blocks = (int)(total / (256 * 2 * 4));
+  blocks = blocks < 1 ? 1 : blocks > 8 ? 8 : blocks;
+  if (a.max_evict > 0 && !fit && most <= 4 && units >= 256) blocks = most;
+  const int groups = (most + blocks - 1) / blocks;
+  const bool fused = !prefill && (fit || groups == 1);
+  if (a.max_evict > 0 && !fused) {
     hipLaunchKernelGGL(evict_kernel<F>, dim3(units * a.max_evict), dim3(64), 0, a.stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (a.n_new >= kPrefillMinTokens && sizeof(typename Fmt<F>::Elem) == 2) return launch_prefill(a);
-  if (a.n_new > 0) {
-    const int ngroups = (a.n_new + kTPW - 1) / kTPW;
-    hipLaunchKernelGGL((insert_kernel<F, kTPW>), dim3((int64_t)units * ngroups), dim3(64), 0,
-                       a.stream, a);
+  if (prefill) return launch_prefill(a);
+  if (most > 0) {
+    hipLaunchKernelGGL(insert_kernel<F>, dim3((int64_t)units * groups), dim3(64 * kInsWaves), 0,
+                       a.stream, a, groups, blocks, bt, fused && a.max_evict > 0);
     return hipGetLastError();
   }
   return hipSuccess;

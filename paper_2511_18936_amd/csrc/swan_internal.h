@@ -133,7 +133,8 @@ struct CompressLaunch {
 constexpr int kStepQG = 8;
 hipError_t launch_compress(const CompressLaunch& a);
 // prefill path (fp16, many tokens): int8 MFMA rotation, two lanes per token's top-k
-constexpr int kPrefillMinTokens = 64;
+constexpr int kPrefillMinTokens = 256;
+constexpr int kPrefillMinBlocks = 512;  // of 64 positions, over all sequences, heads and roles
 hipError_t launch_prefill(const CompressLaunch& a);
 
 // run-time change of k: one launch per role, over the role's page arrays
