@@ -7,13 +7,18 @@
 //                  upper triangle, the rows in up to kGramChunks chunks, one
 //                  workgroup per quadrant and chunk
 //   reduce_kernel  the chunks' partial sums, in order
+//   qr_kernel      G = Q R by Householder reflections, one workgroup per problem
+//   similar_kernel A = R Q = Q^T G Q, and Q, row by row: one step of the QR
+//                  iteration, which orders the diagonal and takes most of the
+//                  off-diagonal mass (without it a spectrum like that of keys, each
+//                  value 0.94 of the last, took 16 sweeps; with it 7)
 //   jacobi_kernel  parallel cyclic Jacobi in float64, one workgroup per problem:
 //                  round-robin pairing, 64 disjoint rotations per round, 127
 //                  rounds per sweep, until the off-diagonal mass is negligible;
 //                  the rotations (one float each) are recorded, not applied to
 //                  the eigenvectors
-//   vector_kernel  the recorded rotations applied to the identity: every row of
-//                  the eigenvector matrix on its own, one wave per row
+//   vector_kernel  the recorded rotations applied to Q: every row of the
+//                  eigenvector matrix on its own, one wave per row
 //   finish_kernel  columns ordered by eigenvalue (descending, stable), signs
 //                  canonicalised (largest-magnitude entry positive, lowest row
 //                  on ties), sigma = sqrt(lambda), P written in float32
@@ -25,9 +30,12 @@
 // sits at positions 2 i and 2 i + 1, a round reads each 2 x 2 block of the
 // upper triangle once, rotates it from both sides and writes its elements where
 // the next round's positions put them, in a second buffer, all addresses fixed
-// for the whole solve: 1.1 us.  One head's 4096 rows: 2.26 ms (16 sweeps), from
-// 11.8 ms; a layer of 8 kv heads (16 problems of 5 k and 17 k rows, side by side
-// instead of one after another): 2.70 ms, from 190 ms.
+// for the whole solve: 1.03 us.  One head's 4096 rows: 1.45 ms (7 sweeps; 2.26
+// ms and 16 sweeps without the QR step), from 11.8 ms; a layer of 8 kv heads (16
+// problems of 5 k and 17 k rows, side by side instead of one after another): 2.16
+// ms (2.70 ms without the QR step), from 190 ms.
+#include <type_traits>
+
 #include "swan_device.h"
 #include "swan_internal.h"
 
@@ -45,7 +53,8 @@ constexpr int kQuad = 64 * 64;                         // elements of a quadrant
 // its quadrant, 4 rows of S per step.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int64_t chunk_rows_of(int64_t n_rows) {  // a multiple of a step's 16
-  return ((n_rows + kGramChunks - 1) / kGramChunks + 15) / 16 * 16;
+  const int64_t r = ((n_rows + kGramChunks - 1) / kGramChunks + 15) / 16 * 16;
+  return r < 256 ? 256 : r;
 }
 
 __global__ __launch_bounds__(256) void gram_kernel(CalibLaunch a) {
@@ -60,18 +69,27 @@ __global__ __launch_bounds__(256) void gram_kernel(CalibLaunch a) {
   if (r0 >= n) return;
   const int64_t r1 = r0 + chunk_rows < n ? r0 + chunk_rows : n;
   f64x4 acc[2][2] = {};
-  for (int64_t r = r0; r < r1; r += 16) {
-    float x[4][4];  // [step][i0, i0 + 16, j0, j0 + 16]
+  float next[4][4];  // [step][i0, i0 + 16, j0, j0 + 16], 16 rows ahead
+  auto load = [&](int64_t r) {
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int64_t row = r + 4 * s + k;
       const float* p = S + row * kD + m;
       const bool in = row < r1;
-      x[s][0] = in ? p[i0] : 0.f;
-      x[s][1] = in ? p[i0 + 16] : 0.f;
-      x[s][2] = in ? p[j0] : 0.f;
-      x[s][3] = in ? p[j0 + 16] : 0.f;
+      next[s][0] = in ? p[i0] : 0.f;
+      next[s][1] = in ? p[i0 + 16] : 0.f;
+      next[s][2] = in ? p[j0] : 0.f;
+      next[s][3] = in ? p[j0 + 16] : 0.f;
     }
+  };
+  load(r0);
+  for (int64_t r = r0; r < r1; r += 16) {
+    float x[4][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[s][i] = next[s][i];
+    load(r + 16);
 #pragma unroll
     for (int s = 0; s < 4; ++s)
 #pragma unroll
@@ -111,6 +129,161 @@ __global__ __launch_bounds__(256) void reduce_kernel(CalibLaunch a) {
 #pragma unroll 8
   for (int c = 0; c < chunks; ++c) sum += p[(int64_t)c * 3 * kQuad];
   a.gram[(int64_t)prob * kD * kD + e] = sum;
+}
+
+// ---------------------------------------------------------------------------
+// One QR step
+// ---------------------------------------------------------------------------
+constexpr int kQrGroups = 8;                   // threads per column
+constexpr int kQrRows = kD / kQrGroups;        // rows a thread holds
+
+// Householder vectors of a problem (row k: vector k, zero below index k), then
+// their factors 2 / v^T v, in the partials' place until the Jacobi rotations come
+__device__ __forceinline__ double* reflectors(const CalibLaunch& a, int prob) {
+  return a.part + (int64_t)prob * kCalibPart;
+}
+
+// Thread (j, g) holds rows 16 g .. of column j in registers; LDS carries the
+// column to eliminate (zero above the diagonal), its dot products with every
+// column (its own square norm among them, so that a step has two barriers) and
+// row k.  What is left below the diagonal by a skipped step stays in the matrix:
+// Q^T G is what is written, whatever its zeros.  2.7 us a step, the chain of its
+// two reductions (3.4 us with the matrix in LDS).
+__global__ __launch_bounds__(1024) void qr_kernel(CalibLaunch a) {
+  __shared__ __attribute__((aligned(16))) double xcol[2][kD];
+  __shared__ double part[kQrGroups][kD];
+  __shared__ double krow[kD];
+  __shared__ double red[2];
+  const int tid = threadIdx.x, prob = blockIdx.x;
+  const int j = tid & (kD - 1), g = tid >> 7;
+  double* G = a.gram + (int64_t)prob * kD * kD;
+  double* V = reflectors(a, prob);
+  double m[kQrRows];
+#pragma unroll
+  for (int r = 0; r < kQrRows; ++r) m[r] = G[(kQrRows * g + r) * kD + j];
+  // columns of less than 1e-30 of the largest diagonal element are left alone (what
+  // remains of a matrix of low rank; their squares would underflow step by step)
+  double dm = tid < kD ? G[tid * kD + tid] : 0.0;
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) dm = fmax(dm, __shfl_xor(dm, o, 64));
+  if ((tid & 63) == 0 && tid < kD) red[tid >> 6] = dm;
+  if (j == 0)
+#pragma unroll
+    for (int r = 0; r < kQrRows; ++r) xcol[0][kQrRows * g + r] = m[r];
+  __syncthreads();
+  dm = fmax(red[0], red[1]);
+  const double tiny = 1e-60 * dm * dm;
+  for (int k = 0; k < kD - 1; ++k) {
+    const double* xc = xcol[k & 1];
+    double dot = 0.0;
+#pragma unroll
+    for (int r = 0; r < kQrRows; r += 2) {
+      const double2 v = *(const double2*)&xc[kQrRows * g + r];
+      dot = fma(v.x, m[r], dot);
+      dot = fma(v.y, m[r + 1], dot);
+    }
+    part[g][j] = dot;
+    const int kr = k - kQrRows * g;  // row k in this thread's rows, if it has it
+    if (kr >= 0 && kr < kQrRows) {   // uniform over the wave
+      double mk = m[0];
+#pragma unroll
+      for (int r = 1; r < kQrRows; ++r) mk = kr == r ? m[r] : mk;
+      krow[j] = mk;
+    }
+    __syncthreads();
+    double sk = 0.0, sj = 0.0;
+#pragma unroll
+    for (int q = 0; q < kQrGroups; ++q) {
+      sk += part[q][k];
+      sj += part[q][j];
+    }
+    const double xk = xc[k];
+    const bool on = sk > xk * xk && sk > tiny;  // something below the diagonal (uniform)
+    // square root and reciprocal by two Newton steps on the hardware's estimates:
+    // every wave computes them, in a sixth of the library's instructions
+    double rs = __builtin_amdgcn_rsq(on ? sk : 1.0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) rs = rs * fma(-0.5 * sk * rs, rs, 1.5);
+    const double norm = sk * rs;
+    const double alpha = xk >= 0.0 ? -norm : norm;
+    const double den = fma(fabs(xk), norm, sk);
+    double beta = __builtin_amdgcn_rcp(on ? den : 1.0);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) beta = beta * fma(-den, beta, 2.0);
+    beta = on ? beta : 0.0;
+    // v = x - alpha e_k; the columns before k are done
+    const double w = j >= k && on ? beta * (sj - alpha * krow[j]) : 0.0;
+#pragma unroll
+    for (int r = 0; r < kQrRows; r += 2) {
+      const double2 x = *(const double2*)&xc[kQrRows * g + r];
+      m[r] = fma(-(kr == r ? xk - alpha : x.x), w, m[r]);
+      m[r + 1] = fma(-(kr == r + 1 ? xk - alpha : x.y), w, m[r + 1]);
+    }
+    if (on && j == k)
+#pragma unroll
+      for (int r = 0; r < kQrRows; ++r) m[r] = kr > r ? m[r] : kr == r ? alpha : 0.0;
+    if (j == k + 1)
+#pragma unroll
+      for (int r = 0; r < kQrRows; ++r)
+        xcol[(k + 1) & 1][kQrRows * g + r] = kr + 1 <= r ? m[r] : 0.0;
+    if (tid < kD) V[k * kD + tid] = tid == k ? xk - alpha : xc[tid];
+    if (tid == 0) V[kD * kD + k] = beta;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int r = 0; r < kQrRows; ++r) G[(kQrRows * g + r) * kD + j] = m[r];
+}
+
+// the sum of v over the wave, in every lane
+__device__ __forceinline__ double wave_sum_f64(double v) {
+  auto step = [](double x, auto ctrl, auto rows) {
+    const int64_t b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, decltype(ctrl)::value,
+                                               decltype(rows)::value, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), decltype(ctrl)::value,
+                                               decltype(rows)::value, 0xF, false);
+    return x + __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+  };
+  v = step(v, std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});
+  v = step(v, std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+  v = step(v, std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+  v = step(v, std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+  v = step(v, std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});
+  v = step(v, std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});
+  const int64_t b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, 63);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
+}
+
+// Row r < kD: row r of Q^T G times Q, in place; row kD + r: row r of Q.  One wave
+// per row, lane l holds columns 2 l and 2 l + 1; grid (2 kD / 4, problems).
+__global__ __launch_bounds__(256) void similar_kernel(CalibLaunch a) {
+  const int lane = threadIdx.x & 63, prob = blockIdx.y;
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int r = row & (kD - 1);
+  double2* out = (double2*)((row < kD ? a.gram : a.vecs) + (int64_t)prob * kD * kD + r * kD);
+  const double* V = reflectors(a, prob);
+  const double2* v = (const double2*)V + lane;
+  double2 x = make_double2(r == 2 * lane ? 1.0 : 0.0, r == 2 * lane + 1 ? 1.0 : 0.0);
+  if (row < kD) x = out[lane];
+  constexpr int kAhead = 4;
+  double2 next[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) next[i] = v[i * kPairs];
+  for (int k0 = 0; k0 < kD - 1; k0 += kAhead) {
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) {
+      const int k = k0 + i;
+      if (k >= kD - 1) break;  // uniform
+      const double2 h = next[i];
+      if (k + kAhead < kD - 1) next[i] = v[(k + kAhead) * kPairs];
+      const double w = V[kD * kD + k] * wave_sum_f64(fma(x.x, h.x, x.y * h.y));
+      x.x = fma(-w, h.x, x.x);
+      x.y = fma(-w, h.y, x.y);
+    }
+  }
+  out[lane] = x;
 }
 
 // ---------------------------------------------------------------------------
@@ -326,8 +499,7 @@ __device__ __forceinline__ double wave_shift(double edge, double v) {
   return __longlong_as_double(((int64_t)hi << 32) | (uint32_t)lo);
 }
 
-// Row r of the eigenvector matrix: row r of the identity times the recorded
-// rotations.  One wave per row, lane i holds positions 2 i and 2 i + 1; the
+// Row r of the eigenvector matrix: row r of Q times the recorded rotations.  One wave per row, lane i holds positions 2 i and 2 i + 1; the
 // players' move is a shift by one lane.  Grid (rows / 4, problems).  A chain of
 // ~20 instructions per round, the rotations read 8 rounds ahead.
 __global__ __launch_bounds__(256) void vector_kernel(CalibLaunch a) {
@@ -335,7 +507,9 @@ __global__ __launch_bounds__(256) void vector_kernel(CalibLaunch a) {
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
   const int rounds = a.status[2 * prob + 1] * kRounds;
   const float* rec = (const float*)(a.part + (int64_t)prob * kGramChunks * 3 * kQuad) + lane;
-  double x = row == 2 * lane ? 1.0 : 0.0, y = row == 2 * lane + 1 ? 1.0 : 0.0;
+  double2* out = (double2*)(a.vecs + (int64_t)prob * kD * kD + (int64_t)row * kD);
+  const double2 q = out[lane];
+  double x = q.x, y = q.y;
   constexpr int kAhead = 8;
   float next[kAhead];
 #pragma unroll
@@ -358,7 +532,6 @@ __global__ __launch_bounds__(256) void vector_kernel(CalibLaunch a) {
       y = wave_shift<0x130>(xr, yr);                   // from lane l + 1; the last upper one down
     }
   }
-  double2* out = (double2*)(a.vecs + (int64_t)prob * kD * kD + (int64_t)row * kD);
   out[lane] = make_double2(x, y);
 }
 
@@ -401,6 +574,10 @@ hipError_t launch_calibrate(const CalibLaunch& a) {
   hipLaunchKernelGGL(gram_kernel, dim3(3, kGramChunks, a.count), dim3(256), 0, a.stream, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(reduce_kernel, dim3(kD * kD / 256, a.count), dim3(256), 0, a.stream, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(qr_kernel, dim3(a.count), dim3(1024), 0, a.stream, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(similar_kernel, dim3(2 * kD / 4, a.count), dim3(256), 0, a.stream, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   e = hipFuncSetAttribute((const void*)jacobi_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                           kJacobiLds);

@@ -187,7 +187,8 @@ constexpr int kGramChunks = 32;
 constexpr size_t kCalibPart = (size_t)kGramChunks * 3 * 64 * 64;
 constexpr size_t kCalibWorkspace = sizeof(double) * (2 * kD * kD + kD + kCalibPart + 32);
 static_assert(kCalibPart * sizeof(double) >=
-                  (size_t)kJacobiMaxSweeps * (kD - 1) * (kD / 2) * sizeof(float),
-              "the rotations take the partials' place");
+                  (size_t)kJacobiMaxSweeps * (kD - 1) * (kD / 2) * sizeof(float) &&
+                  kCalibPart >= (size_t)kD * kD + kD,
+              "the reflectors, then the rotations, take the partials' place");
 
 }  // namespace swan
