@@ -106,25 +106,33 @@ class SwanAttentionLayer:
     def project(self, x):
         """Post-RoPE q [B][H_q][n][128], k and v_hat [B][H_kv][n][128] of new rows x
         [B][n][hidden] at each sequence's next positions."""
-        B, n, _ = x.shape
-        d = HEAD_DIM
-        pos0 = list(self.cache.seq_len)
         qkv = x @ self.W_qkv
-        nq, nkv = self.n_heads * d, self.n_kv_heads * d
-        q = qkv[..., :nq].reshape(B, n, self.n_heads, d).transpose(1, 2).contiguous()
-        k = qkv[..., nq:nq + nkv].reshape(B, n, self.n_kv_heads, d).transpose(1, 2).contiguous()
-        v = qkv[..., nq + nkv:].reshape(B, n, self.n_kv_heads, d).transpose(1, 2).contiguous()
-        swan.rope(q, pos0, self.rope_base, out=q)
-        swan.rope(k, pos0, self.rope_base, out=k)
-        return q, k, v
+        nq, nkv = self.n_heads * HEAD_DIM, self.n_kv_heads * HEAD_DIM
+        return (self._rows(qkv[..., :nq], self.n_heads, True),
+                self._rows(qkv[..., nq:nq + nkv], self.n_kv_heads, True),
+                self._rows(qkv[..., nq + nkv:], self.n_kv_heads, False))
+
+    def _rows(self, t, heads: int, rope: bool):
+        """[B][n][heads 128] projections as [B][heads][n][128], rotated by RoPE at the
+        sequences' next positions."""
+        B, n, _ = t.shape
+        t = t.reshape(B, n, heads, HEAD_DIM).transpose(1, 2).contiguous()
+        if rope:
+            swan.rope(t, self.cache.seq_len, self.rope_base, out=t)
+        return t
 
     def __call__(self, x):
         """x [B][n][hidden]: append the n rows of every sequence to the cache; for a
         decode step (n = 1) return y [B][hidden], the layer's attention output."""
-        q, k, v = self.project(x)
         if x.shape[1] != 1:
-            self.cache.append(k, v, self.P_qk, None)
+            # only the keys and values of a prompt are used (its attention is not part
+            # of this layer): for 32 query and 8 KV heads a third of the projections
+            nq, nkv = self.n_heads * HEAD_DIM, self.n_kv_heads * HEAD_DIM
+            kv = x @ self.W_qkv[:, nq:]
+            self.cache.append(self._rows(kv[..., :nkv], self.n_kv_heads, True),
+                              self._rows(kv[..., nkv:], self.n_kv_heads, False), self.P_qk, None)
             return None
+        q, k, v = self.project(x)
         B = x.shape[0]
         o_hat = self.cache.step(k, v, q[:, :, 0].contiguous(), self.P_qk, None)
         return o_hat.view(B, self.n_heads * HEAD_DIM) @ self.W_o_hat
