@@ -46,6 +46,10 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
         raise ValueError("k and v must be [n_kv_heads][n][128]")
     if W_o.dim() != 2 or W_o.shape[0] != n_q * d:
         raise ValueError("W_o must be [N_q * 128][hidden]")
+    for name, out in (("P_qk_out", P_qk_out), ("P_vo_out", P_vo_out)):
+        for j in range(n_kv_heads):
+            if out[j].dtype != torch.float32 or not out[j].is_cuda or out[j].numel() != d * d:
+                raise ValueError(f"{name}[{j}] must be a [128][128] float32 cuda matrix")
     G = n_q // n_kv_heads
     hidden = W_o.shape[1]
     q_grouped = q.reshape(n_kv_heads, n * G, d)
@@ -60,16 +64,19 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     wo_t = W_o.reshape(n_kv_heads, G, d, hidden).transpose(2, 3)  # W_O^(h) transposed
     s_vo[:, n:].unflatten(1, (G, hidden)).copy_(wo_t)
     P = torch.empty((2 * n_kv_heads, d, d), dtype=torch.float32, device=q.device)
+    on = torch.cuda.current_stream(q.device)
     if stream is not None:  # the stacking above ran on the current stream
-        stream.wait_stream(torch.cuda.current_stream(q.device))
-    swan.calibrate_rotations(s, [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads, P,
-                             stream=stream)
-    for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
-        if isinstance(out, torch.Tensor):
-            out.copy_(got)
-        else:  # a list of matrices
-            for j in range(n_kv_heads):
-                out[j].copy_(got[j])
+        stream.wait_stream(on)
+        on = stream
+    swan.calibrate_rotations(s, [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads, P, stream=on)
+    with torch.cuda.stream(on):
+        for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
+            if isinstance(out, torch.Tensor):
+                out[:n_kv_heads].copy_(got.view(out[:n_kv_heads].shape))
+            else:  # a list of matrices
+                for j in range(n_kv_heads):
+                    out[j].copy_(got[j])
+    on.synchronize()  # the rotations are in place on return, for any stream
 
 
 class SwanAttentionLayer:

@@ -41,3 +41,35 @@ def test_batch_equals_single_calls(gpu_device, swan_mod, torch_mod):
         if ref is not None:
             # float64 solve: 1e-15 of the largest eigenvalue, in sigma^2
             assert np.max(np.abs(got - ref)) <= 1e-6 * ref[0] + 1e-30
+
+
+def test_joint_outputs(gpu_device, torch_mod):
+    """calibrate_joint into arrays of more heads than the layer's, into lists of matrices
+    and on a stream of the caller's: the same matrices, in place on return; an output of
+    another type is refused."""
+    from paper_2511_18936_amd.layer import calibrate_joint
+
+    torch = torch_mod
+    Hq, Hkv, n, hidden = 4, 2, 70, 96
+    gen = torch.Generator(device=gpu_device).manual_seed(5)
+    rnd = lambda *s: torch.randn(s, device=gpu_device, generator=gen)
+    args = (rnd(Hq, n, 128), rnd(Hkv, n, 128), rnd(Hkv, n, 128), rnd(Hq * 128, hidden), Hkv)
+    ref = [torch.empty((Hkv, 128, 128), device=gpu_device) for _ in range(2)]
+    calibrate_joint(*args, *ref)
+
+    large = [torch.full((Hkv + 1, 128, 128), 7.0, device=gpu_device) for _ in range(2)]
+    calibrate_joint(*args, *large)
+    lists = [[torch.empty((128, 128), device=gpu_device) for _ in range(Hkv)] for _ in range(2)]
+    calibrate_joint(*args, *lists)
+    side = torch.cuda.Stream()
+    other = [torch.zeros((Hkv, 128, 128), device=gpu_device) for _ in range(2)]
+    torch.cuda.synchronize()
+    calibrate_joint(*args, *other, stream=side)
+    with torch.cuda.stream(torch.cuda.Stream()):  # waits for neither stream
+        seen = [t.cpu() for t in other]
+    for i in range(2):
+        assert torch.equal(large[i][:Hkv], ref[i]) and torch.all(large[i][Hkv] == 7.0)
+        assert torch.equal(torch.stack(lists[i]), ref[i])
+        assert torch.equal(seen[i], ref[i].cpu())
+    with pytest.raises(ValueError):
+        calibrate_joint(*args, ref[0].half(), ref[1])
