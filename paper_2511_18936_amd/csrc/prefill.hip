@@ -814,8 +814,9 @@ void prefill_kernel(CompressLaunch a, int units_per_wave) {
 // Units of 32 positions per wave: a workgroup's set-up (P's digits, ~4 us) is
 // paid once for all of its waves' units, so long prompts take 16; but the GPU
 // runs one workgroup per compute unit, so a batch that would leave it in fewer
-// than 4 rounds of workgroups takes fewer units each, down to one: a prompt of
-// 1009 tokens on 8 kv heads takes 30 us (201 us with 8 blocks of 64 per wave).
+// than 4 rounds of workgroups takes fewer units each, down to one: 1009 tokens on
+// 8 kv heads took 30 us here (201 us with 8 blocks of 64 per wave; the insert
+// kernel, which such a prompt goes to, takes 18 us).
 static int units_per_wave(int64_t total_units) {
   int64_t n = total_units / ((int64_t)kCus * kPrefillWaves * 4);
   return n < 1 ? 1 : n > 16 ? 16 : (int)n;
