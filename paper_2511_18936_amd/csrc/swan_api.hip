@@ -496,6 +496,7 @@ swan_status swan_calibrate_rotations(const float* rows, int32_t count,
     a.part = a.vecs + a.count * kMat;
     a.lam = a.part + a.count * swan::kCalibPart;
     a.status = (int32_t*)(a.lam + (size_t)a.count * swan::kD);
+    a.graded = a.status + 2 * a.count;
     hipError_t e = swan::launch_calibrate(a);
     if (e != hipSuccess) return hip_status(e, "calibrate launch");
     int32_t st_host[2 * swan::kMaxCalib] = {};  // each problem's (converged, sweeps)

@@ -178,12 +178,13 @@ struct CalibLaunch {
   double* lam;        // [count][128]
   double* part;       // [count][kGramChunks][3][64][64]; then the Jacobi rotations
   int32_t* status;    // [count][2]: converged, sweeps
+  int32_t* graded;    // [count]: the diagonal of G is graded
   hipStream_t stream;
 };
 hipError_t launch_calibrate(const CalibLaunch& a);
 constexpr int kJacobiMaxSweeps = 40;
 constexpr int kGramChunks = 32;
-// workspace per problem, in doubles: gram, vecs, lam, partials, status
+// workspace per problem, in doubles: gram, vecs, lam, partials, status and graded
 constexpr size_t kCalibPart = (size_t)kGramChunks * 3 * 64 * 64;
 constexpr size_t kCalibWorkspace = sizeof(double) * (2 * kD * kD + kD + kCalibPart + 32);
 static_assert(kCalibPart * sizeof(double) >=

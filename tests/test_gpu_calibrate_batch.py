@@ -43,6 +43,43 @@ def test_batch_equals_single_calls(gpu_device, swan_mod, torch_mod):
             assert np.max(np.abs(got - ref)) <= 1e-6 * ref[0] + 1e-30
 
 
+@pytest.mark.parametrize("flat", [True, False])
+def test_channels_of_other_scales(gpu_device, swan_mod, torch_mod, flat):
+    """Columns of S that differ in scale (outlier and nearly dead channels): the basis
+    and each singular value to the float32 they are written in, also among the small
+    channels, in one call with a problem whose columns have one scale."""
+    torch = torch_mod
+    rng = np.random.default_rng(11)
+    scales, S = (1.0, 0.2, 1e-2, 1e-4, 1e-5, 1e-6, 1e-7), []
+    for s in scales:
+        x = rng.standard_normal((512, 128))
+        if not flat:  # a falling spectrum in a rotated basis
+            x = (x * np.exp(-np.arange(128) / 16)) @ si.haar_orthogonal(rng, 128)
+        x[:, rng.permutation(128)[:16]] *= s
+        if s == 1e-4:
+            x[:, :2] *= 50.0
+        S.append(x.astype(np.float32))
+    P = torch.empty((len(S), 128, 128), device=gpu_device)
+    sig = torch.empty((len(S), 128), device=gpu_device)
+    swan_mod.calibrate_rotations(torch.tensor(np.concatenate(S), device=gpu_device),
+                                 [512] * len(S), P, sig)
+    for i, s in enumerate(scales):
+        Po, so = O.calibrate(S[i])
+        got = P[i].double().cpu().numpy()
+        # signs by the oracle's column (its largest entry may tie to rounding)
+        err = np.sqrt(np.sum((got * np.sign(np.sum(got * Po, axis=0)) - Po) ** 2, axis=0))
+        # float32 P: 2^-24 of a unit column, doubled; the oracle's own float64 SVD:
+        # 2^-53 of the largest singular value against the distance to the next one
+        # (its square root of eigenvalues costs the rotated spectrum's 1 / 3000
+        # smallest values another 1e-8 here)
+        d = np.abs(np.diff(so))
+        gap = np.minimum(np.r_[np.inf, d], np.r_[d, np.inf])
+        tol = 2.0 ** -23 + 2.0 ** -53 * so[0] / gap + (0 if flat else 3e-8)
+        assert np.all(err <= tol), (s, np.max(err / tol), np.max(err))
+        rel = np.abs(sig[i].double().cpu().numpy() - so) / so
+        assert np.all(rel <= 2.0 ** -23 + 2.0 ** -50 * so[0] / so), (s, np.max(rel))
+
+
 def test_joint_outputs(gpu_device, torch_mod):
     """calibrate_joint into arrays of more heads than the layer's, into lists of matrices
     and on a stream of the caller's: the same matrices, in place on return; an output of
