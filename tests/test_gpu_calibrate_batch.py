@@ -110,3 +110,35 @@ def test_joint_outputs(gpu_device, torch_mod):
         assert torch.equal(seen[i], ref[i].cpu())
     with pytest.raises(ValueError):
         calibrate_joint(*args, ref[0].half(), ref[1])
+
+
+def _joint_args(torch, device, Hq=4, Hkv=2, n=70, hidden=96):
+    gen = torch.Generator(device=device).manual_seed(5)
+    rnd = lambda *s: torch.randn(s, device=device, generator=gen)
+    return [rnd(Hq, n, 128), rnd(Hkv, n, 128), rnd(Hkv, n, 128), rnd(Hq * 128, hidden), Hkv]
+
+
+def _joint_outputs(torch, device, Hkv=2):
+    return [torch.zeros((Hkv, 128, 128), device=device) for _ in range(2)]
+
+
+def test_joint_of_parameters(gpu_device, torch_mod):
+    """W_o and the outputs may be a model's parameters, or made under inference mode."""
+    from paper_2511_18936_amd.layer import calibrate_joint
+
+    torch = torch_mod
+    args, ref = _joint_args(torch, gpu_device), _joint_outputs(torch, gpu_device)
+    calibrate_joint(*args, *ref)
+    args[3] = torch.nn.Parameter(args[3])
+    params = [torch.nn.Parameter(t) for t in _joint_outputs(torch, gpu_device)]
+    calibrate_joint(*args, *params)
+    lists = [[torch.nn.Parameter(m.clone()) for m in t] for t in _joint_outputs(torch, gpu_device)]
+    calibrate_joint(*args, *lists)
+    with torch.inference_mode():
+        inf = _joint_outputs(torch, gpu_device)
+    calibrate_joint(*args, *inf)
+    for i in range(2):
+        assert params[i].requires_grad and params[i].is_leaf
+        assert torch.equal(params[i].detach(), ref[i])
+        assert torch.equal(torch.stack([m.detach() for m in lists[i]]), ref[i])
+        assert torch.equal(inf[i], ref[i])
