@@ -48,8 +48,14 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
         raise ValueError("W_o must be [N_q * 128][hidden]")
     for name, out in (("P_qk_out", P_qk_out), ("P_vo_out", P_vo_out)):
         for j in range(n_kv_heads):
-            if out[j].dtype != torch.float32 or not out[j].is_cuda or out[j].numel() != d * d:
+            m = out[j]
+            if m.dtype != torch.float32 or not m.is_cuda:
                 raise ValueError(f"{name}[{j}] must be a [128][128] float32 cuda matrix")
+            swan._tensor(m, name, torch.float32, (d, d))
+    swan._on_gpu(q=q)
+    if any(t.device != q.device for t in (k, v, W_o)):
+        raise ValueError(f"q is on {q.device}, k on {k.device}, v on {v.device}, "
+                         f"W_o on {W_o.device}: all must be on one GPU")
     # autograd has no part in this: W_o and the outputs may be parameters
     with torch.inference_mode():
         G = n_q // n_kv_heads

@@ -142,3 +142,25 @@ def test_joint_of_parameters(gpu_device, torch_mod):
         assert torch.equal(params[i].detach(), ref[i])
         assert torch.equal(torch.stack([m.detach() for m in lists[i]]), ref[i])
         assert torch.equal(inf[i], ref[i])
+
+
+def test_joint_refusals(gpu_device, swan_mod, torch_mod):
+    """An output of another shape or layout, or an input on another device, is refused
+    before anything is enqueued."""
+    from paper_2511_18936_amd.layer import calibrate_joint
+
+    torch = torch_mod
+    args, ref = _joint_args(torch, gpu_device), _joint_outputs(torch, gpu_device)
+    flat = torch.zeros((2, 128 * 128), device=gpu_device)
+    wide = torch.zeros((2, 128, 256), device=gpu_device)[:, :, ::2]
+    turned = torch.zeros((2, 128, 128), device=gpu_device).transpose(1, 2)
+    for bad in (flat, wide, turned, [turned[0], ref[0][1]]):
+        for out in ((bad, ref[1]), (ref[0], bad)):
+            with pytest.raises(swan_mod.SwanError):
+                calibrate_joint(*args, *out)
+    for i in range(4):
+        moved = list(args)
+        moved[i] = args[i].cpu()
+        with pytest.raises((ValueError, swan_mod.SwanError)):
+            calibrate_joint(*moved, *ref)
+    assert not any(t.any() for t in ref + [flat, wide, turned])
