@@ -56,10 +56,14 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     if any(t.device != q.device for t in (k, v, W_o)):
         raise ValueError(f"q is on {q.device}, k on {k.device}, v on {v.device}, "
                          f"W_o on {W_o.device}: all must be on one GPU")
+    G = n_q // n_kv_heads
+    hidden = W_o.shape[1]
+    on = torch.cuda.current_stream(q.device)
+    if stream is not None:  # the inputs may come from either stream
+        stream.wait_stream(on)
+        on = stream
     # autograd has no part in this: W_o and the outputs may be parameters
-    with torch.inference_mode():
-        G = n_q // n_kv_heads
-        hidden = W_o.shape[1]
+    with torch.inference_mode(), torch.cuda.stream(on):
         q_grouped = q.reshape(n_kv_heads, n * G, d)
         # every joint matrix in one array, S_QK of the heads, then S_VO, solved side by side
         rows_qk, rows_vo = n * (G + 1), n + G * hidden
@@ -72,19 +76,14 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
         wo_t = W_o.reshape(n_kv_heads, G, d, hidden).transpose(2, 3)  # W_O^(h) transposed
         s_vo[:, n:].unflatten(1, (G, hidden)).copy_(wo_t)
         P = torch.empty((2 * n_kv_heads, d, d), dtype=torch.float32, device=q.device)
-        on = torch.cuda.current_stream(q.device)
-        if stream is not None:  # the stacking above ran on the current stream
-            stream.wait_stream(on)
-            on = stream
         swan.calibrate_rotations(s, [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads, P, stream=on)
-        with torch.cuda.stream(on):
-            for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
-                if isinstance(out, torch.Tensor):
-                    out[:n_kv_heads].copy_(got.view(out[:n_kv_heads].shape))
-                else:  # a list of matrices
-                    for j in range(n_kv_heads):
-                        out[j].copy_(got[j])
-        on.synchronize()  # the rotations are in place on return, for any stream
+        for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
+            if isinstance(out, torch.Tensor):
+                out[:n_kv_heads].copy_(got.view(out[:n_kv_heads].shape))
+            else:  # a list of matrices
+                for j in range(n_kv_heads):
+                    out[j].copy_(got[j])
+    on.synchronize()  # the rotations are in place on return, for any stream
 
 
 class SwanAttentionLayer:

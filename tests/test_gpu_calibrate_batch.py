@@ -164,3 +164,26 @@ def test_joint_refusals(gpu_device, swan_mod, torch_mod):
         with pytest.raises((ValueError, swan_mod.SwanError)):
             calibrate_joint(*moved, *ref)
     assert not any(t.any() for t in ref + [flat, wide, turned])
+
+
+def test_joint_inputs_of_the_given_stream(gpu_device, torch_mod):
+    """Inputs still being written on the caller's stream are read after that."""
+    from paper_2511_18936_amd.layer import calibrate_joint
+
+    torch = torch_mod
+    args, ref = _joint_args(torch, gpu_device), _joint_outputs(torch, gpu_device)
+    calibrate_joint(*args, *ref)
+    late = [torch.zeros_like(t) for t in args[:4]]
+    got = _joint_outputs(torch, gpu_device)
+    big = torch.randn((4096, 4096), device=gpu_device)
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        for _ in range(100):  # some milliseconds before the inputs are there
+            big = (big @ big).clamp_(-1, 1)
+        for dst, src in zip(late, args):
+            dst.copy_(src)
+    calibrate_joint(*late, args[4], *got, stream=side)
+    torch.cuda.synchronize()
+    for i in range(2):
+        assert torch.equal(got[i], ref[i])
