@@ -25,6 +25,10 @@ from . import swan
 
 HEAD_DIM = swan.HEAD_DIM
 
+# joint matrices and solver workspaces that calibrate_joint holds at a time: a layer of
+# 32 kv heads and 4096 calibration tokens at once (0.49 GB), longer ones a few heads at a time
+JOINT_BYTES = 512 << 20
+
 
 def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=None) -> None:
     """The layer's rotations from calibration activations (Sec. 4.1.1-4.1.2).
@@ -36,7 +40,8 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     memory as float32, S_QK = [Q_grouped^(j); K^(j)] and S_VO = [V^(j); W_O^(h)^T
     for the group's heads], W_O^(h) being rows 128 h .. 128 h + 127 of W_o, and
     swan_calibrate_rotations writes their right singular matrices to P_qk_out[j]
-    and P_vo_out[j] ([N_kv][128][128] float32)."""
+    and P_vo_out[j] ([N_kv][128][128] float32).  The matrices are solved side by side in
+    groups of at most JOINT_BYTES, or one at a time where one is larger."""
     import torch
 
     n_q, n, d = q.shape
@@ -65,18 +70,32 @@ def calibrate_joint(q, k, v, W_o, n_kv_heads: int, P_qk_out, P_vo_out, stream=No
     # autograd has no part in this: W_o and the outputs may be parameters
     with torch.inference_mode(), torch.cuda.stream(on):
         q_grouped = q.reshape(n_kv_heads, n * G, d)
-        # every joint matrix in one array, S_QK of the heads, then S_VO, solved side by side
-        rows_qk, rows_vo = n * (G + 1), n + G * hidden
-        s = torch.empty((n_kv_heads * (rows_qk + rows_vo), d), dtype=torch.float32, device=q.device)
-        s_qk = s[:n_kv_heads * rows_qk].view(n_kv_heads, rows_qk, d)
-        s_qk[:, :n * G] = q_grouped
-        s_qk[:, n * G:] = k
-        s_vo = s[n_kv_heads * rows_qk:].view(n_kv_heads, rows_vo, d)
-        s_vo[:, :n] = v
         wo_t = W_o.reshape(n_kv_heads, G, d, hidden).transpose(2, 3)  # W_O^(h) transposed
-        s_vo[:, n:].unflatten(1, (G, hidden)).copy_(wo_t)
+        rows_qk, rows_vo = n * (G + 1), n + G * hidden
+        # the problems, S_QK of the heads, then S_VO; the first p0 of them are done
+        rows = [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads
+        workspace = swan.calibrate_workspace_bytes(d)
         P = torch.empty((2 * n_kv_heads, d, d), dtype=torch.float32, device=q.device)
-        swan.calibrate_rotations(s, [rows_qk] * n_kv_heads + [rows_vo] * n_kv_heads, P, stream=on)
+        p0 = 0
+        while p0 < len(rows):
+            p1, held = p0, 0  # the group p0 .. p1 - 1, in one array, solved side by side
+            while p1 < len(rows):
+                held += 4 * d * rows[p1] + workspace
+                if held > JOINT_BYTES and p1 > p0:
+                    break
+                p1 += 1
+            s = torch.empty((sum(rows[p0:p1]), d), dtype=torch.float32, device=q.device)
+            h0, h1 = min(p0, n_kv_heads), min(p1, n_kv_heads)
+            s_qk = s[:(h1 - h0) * rows_qk].view(h1 - h0, rows_qk, d)
+            s_qk[:, :n * G] = q_grouped[h0:h1]
+            s_qk[:, n * G:] = k[h0:h1]
+            g0, g1 = max(p0 - n_kv_heads, 0), max(p1 - n_kv_heads, 0)
+            s_vo = s[(h1 - h0) * rows_qk:].view(g1 - g0, rows_vo, d)
+            s_vo[:, :n] = v[g0:g1]
+            s_vo[:, n:].unflatten(1, (G, hidden)).copy_(wo_t[g0:g1])
+            swan.calibrate_rotations(s, rows[p0:p1], P[p0:p1], stream=on)
+            del s, s_qk, s_vo  # before the next group's
+            p0 = p1
         for out, got in ((P_qk_out, P[:n_kv_heads]), (P_vo_out, P[n_kv_heads:])):
             if isinstance(out, torch.Tensor):
                 out[:n_kv_heads].copy_(got.view(out[:n_kv_heads].shape))

@@ -187,3 +187,25 @@ def test_joint_inputs_of_the_given_stream(gpu_device, torch_mod):
     torch.cuda.synchronize()
     for i in range(2):
         assert torch.equal(got[i], ref[i])
+
+
+@pytest.mark.parametrize("budget", [1, 16 << 20, 40 << 20])
+def test_joint_memory(gpu_device, torch_mod, monkeypatch, budget):
+    """The joint matrices of many tokens are stacked and solved a group at a time, with the
+    same result."""
+    from paper_2511_18936_amd import layer, swan
+
+    torch = torch_mod
+    args = _joint_args(torch, gpu_device, Hq=6, Hkv=3, n=4096)
+    ref, got = _joint_outputs(torch, gpu_device, 3), _joint_outputs(torch, gpu_device, 3)
+    layer.calibrate_joint(*args, *ref)
+    monkeypatch.setattr(layer, "JOINT_BYTES", budget, raising=False)
+    torch.cuda.synchronize()
+    torch.cuda.reset_peak_memory_stats()
+    before = torch.cuda.memory_allocated()
+    layer.calibrate_joint(*args, *got)
+    peak = torch.cuda.max_memory_allocated() - before
+    for i in range(2):
+        assert torch.equal(got[i], ref[i])
+    one = 3 * 4096 * 128 * 4 + swan.calibrate_workspace_bytes(128)  # an S_QK and its solver
+    assert peak <= max(budget, one) + (1 << 20), peak  # and the rotations
