@@ -154,16 +154,23 @@ class SwanAttentionLayer:
             swan.rope(t, self.cache.seq_len, self.rope_base, out=t)
         return t
 
+    def _prompt_rows(self, x):
+        """project(x) without the queries: a prompt's attention is not part of this layer,
+        and for 32 query and 8 KV heads its keys and values are a third of the projections.
+        A project() of a subclass or of the object itself is called as it is."""
+        if getattr(self.project, "__func__", None) is not SwanAttentionLayer.project:
+            return self.project(x)[1:]
+        nq, nkv = self.n_heads * HEAD_DIM, self.n_kv_heads * HEAD_DIM
+        kv = x @ self.W_qkv[:, nq:]
+        return (self._rows(kv[..., :nkv], self.n_kv_heads, True),
+                self._rows(kv[..., nkv:], self.n_kv_heads, False))
+
     def __call__(self, x):
         """x [B][n][hidden]: append the n rows of every sequence to the cache; for a
         decode step (n = 1) return y [B][hidden], the layer's attention output."""
         if x.shape[1] != 1:
-            # only the keys and values of a prompt are used (its attention is not part
-            # of this layer): for 32 query and 8 KV heads a third of the projections
-            nq, nkv = self.n_heads * HEAD_DIM, self.n_kv_heads * HEAD_DIM
-            kv = x @ self.W_qkv[:, nq:]
-            self.cache.append(self._rows(kv[..., :nkv], self.n_kv_heads, True),
-                              self._rows(kv[..., nkv:], self.n_kv_heads, False), self.P_qk, None)
+            k, v = self._prompt_rows(x)
+            self.cache.append(k, v, self.P_qk, None)
             return None
         q, k, v = self.project(x)
         B = x.shape[0]
