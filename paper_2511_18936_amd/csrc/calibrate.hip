@@ -38,8 +38,8 @@
 // ms (2.70 ms without the QR step), from 190 ms.
 #include <type_traits>
 
+#include "swan_cache_ops.h"
 #include "swan_device.h"
-#include "swan_internal.h"
 
 namespace swan {
 

@@ -25,8 +25,8 @@
 // in ascending order and stores the destination slot 8 entries at a time.
 #include <utility>
 
+#include "swan_cache_ops.h"
 #include "swan_device.h"
-#include "swan_internal.h"
 
 namespace swan {
 

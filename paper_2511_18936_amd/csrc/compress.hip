@@ -25,8 +25,8 @@
 // then numbered in ascending dim order with mbcnt and written to the page.
 #include <type_traits>
 
+#include "swan_cache_ops.h"
 #include "swan_device.h"
-#include "swan_internal.h"
 
 namespace swan {
 

@@ -52,8 +52,8 @@
 // MFMAs of the next tile; the output as a walk over the set bits: 2.51 ms.)
 #include <type_traits>
 
+#include "swan_cache_ops.h"
 #include "swan_device.h"
-#include "swan_internal.h"
 
 namespace swan {
 

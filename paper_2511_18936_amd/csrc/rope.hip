@@ -5,8 +5,8 @@
 // the angle pos * base^(-2j/128) ("rotate half" pairing), computed in float64
 // and rounded once to the storage type, so the rows are what the cache's exact
 // rotation then sees.
+#include "swan_cache_ops.h"
 #include "swan_device.h"
-#include "swan_internal.h"
 
 namespace swan {
 

@@ -11,7 +11,7 @@
 #include <string>
 
 #include "swan.h"
-#include "swan_internal.h"
+#include "swan_cache_ops.h"
 #include "swan_layer.h"
 
 // ---------------------------------------------------------------------------

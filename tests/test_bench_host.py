@@ -1,6 +1,8 @@
 """bench.py's measurement helpers, on the host: the algorithmic byte model behind
 roofline.achieved, the mirror of the library's launch grouping behind
 launches_per_step, and the single-GPU guard."""
+import os
+import re
 import subprocess
 import sys
 
@@ -50,3 +52,21 @@ def test_bench_refuses_several_gpus():
                        capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+def test_attention_sources_are_what_the_attention_includes():
+    """The traffic records hold while bench.ATTN_SOURCES do not change: these are the
+    decode sources and what they include, and no other path's declarations, whose changes
+    would put the records aside for nothing."""
+    csrc = os.path.join(bench.ROOT, "paper_2511_18936_amd", "csrc")
+    seen, todo = {}, [f for f in os.listdir(csrc) if re.fullmatch(r"decode\w*\.hip", f)]
+    while todo:
+        name = todo.pop()
+        if name in seen or not os.path.exists(os.path.join(csrc, name)):  # public headers
+            continue
+        with open(os.path.join(csrc, name)) as f:
+            seen[name] = f.read()
+        todo += re.findall(r'#include "([\w.]+)"', seen[name])
+    assert sorted(seen) == sorted(bench.ATTN_SOURCES)
+    for name, text in seen.items():
+        assert not re.search(r"launch_(compress|prefill|change_k|rope|calibrate)\b", text), name
