@@ -94,12 +94,12 @@ __device__ __forceinline__ void select_and_pack(typename Store<typename Fmt<F>::
   }
 }
 
-__device__ __forceinline__ int evict_begin(int len_old, int bb) {
+__host__ __device__ __forceinline__ int evict_begin(int len_old, int bb) {
   return len_old > bb ? len_old - bb : 0;
 }
 
 // tokens that leave the ring in this call: positions [begin, end)
-__device__ __forceinline__ int evict_end(int len_old, int n_new, int bb) {
+__host__ __device__ __forceinline__ int evict_end(int len_old, int n_new, int bb) {
   const int lim = len_old + n_new - bb;
   return len_old < lim ? len_old : lim;
 }
@@ -513,6 +513,72 @@ __global__ __launch_bounds__(256) void step_kernel(CompressLaunch a) {
   }
 }
 
+// How an append of several tokens runs.
+struct AppendPlan {
+  int kernel;      // kAppend...
+  int bt;          // positions per block
+  int blocks;      // ... per workgroup of insert_kernel
+  int groups;      // workgroups per (sequence, kv head, role) of insert_kernel
+  bool fused;      // insert_kernel evicts; else an eviction launch goes first
+};
+
+static AppendPlan plan_append(const CompressLaunch& a) {
+  AppendPlan pl = {kAppendNone, kPage, 1, 0, false};
+  const int units = a.B * a.Hkv * 2;
+  bool fit = true;  // no new token is pruned
+  int longest = 0, appending = 0;
+  int64_t tokens = 0;  // of the appending sequences
+  for (int b = 0; b < a.B; ++b) {
+    fit = fit && a.tab.nnew[b] <= a.bb;
+    longest = a.tab.nnew[b] > longest ? a.tab.nnew[b] : longest;
+    tokens += a.tab.nnew[b];
+    appending += a.tab.nnew[b] > 0;
+  }
+  // Positions per block: where no new token is pruned, so many that two
+  // workgroups per compute unit share the tokens (8 sequences x 8 kv heads x 40
+  // tokens: 12.4 us with blocks of 16, 16.2 with blocks of 64).
+  if (fit)
+    while (pl.bt > 16 && (int64_t)units * ((longest + pl.bt / 2 - 1) / (pl.bt / 2)) <= 512)
+      pl.bt /= 2;
+  int most = 0;       // blocks of one unit
+  int64_t total = 0;  // blocks of all
+  for (int b = 0; b < a.B; ++b) {
+    const int org = a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
+    const int n = a.tab.nnew[b] ? (a.tab.len[b] + a.tab.nnew[b] - org + pl.bt - 1) / pl.bt : 0;
+    most = n > most ? n : most;
+    total += (int64_t)n * 2 * a.Hkv;
+  }
+  if (most == 0) return pl;
+  // Long appends of binary16 rows go to the prefill kernel: its rotation on int8
+  // MFMA has twice the rate of float64's, but a workgroup first makes P's digits
+  // and takes 256 tokens at a time.  Measured (one unit = a kv head's keys or
+  // values, us, insert / prefill), all sequences with as many tokens: 16 units x
+  // 1024 tokens 19 / 32, 128 x 256 (512 blocks) 29 / 28, 256 x 64 14 / 20, x 160
+  // 46 / 28, x 1024 195 / 115, 1024 x 64 43 / 62, x 160 133 / 91, x 256 195 / 108;
+  // on 1000 cached tokens, 64 of them evicted, 1024 x 96 110 / 117, x 128 131 / 125,
+  // x 160 158 / 125.  Of different lengths (1024 units): 200 and 40 tokens in turn
+  // 180 / 100; 300 for one sequence in 8, else 20: 79 / 166; 1000 for one in 8, else
+  // 20: 471 / 306.  The lengths are the sequences' own, not the rows' stride (64
+  // tokens each in rows for 256: 54 / 74).
+  const bool many = longest >= kPrefillMinTokens || tokens >= (int64_t)kPrefillMinMean * appending;
+  const bool prefill = many && total > kPrefillMinBlocks && a.dtype != SWAN_F32;
+  // Blocks per workgroup: P's columns are loaded once for all of them (~2 us), so
+  // many blocks go up to 8 to a workgroup, as long as the GPU keeps 4 rounds of
+  // two workgroups per compute unit.  Where the units alone fill it, a few blocks
+  // stay together, so that the eviction needs no launch of its own (on 1000 cached
+  // tokens, us, eviction launch / this: 256 units x 100 tokens, buffer 64, 52 / 36,
+  // float32 x 200 80 / 76, x 129, buffer 128, 69 / 72; 1024 units x 200, buffer 128,
+  // 225 / 193; 128 units x 100, buffer 64, 31 / 36).
+  int blocks = (int)(total / (256 * 2 * 4));
+  blocks = blocks < 1 ? 1 : blocks > 8 ? 8 : blocks;
+  if (a.max_evict > 0 && !fit && most <= 4 && units >= 256) blocks = most;
+  pl.kernel = prefill ? kAppendPrefill : kAppendInsert;
+  pl.blocks = blocks;
+  pl.groups = (most + blocks - 1) / blocks;
+  pl.fused = !prefill && (fit || pl.groups == 1);
+  return pl;
+}
+
 template <typename F>
 static hipError_t launch_compress_t(const CompressLaunch& a) {
   const int units = a.B * a.Hkv * 2;
@@ -551,54 +617,17 @@ static hipError_t launch_compress_t(const CompressLaunch& a) {
     }
     return hipGetLastError();
   }
-  bool fit = true;  // no new token is pruned
-  int longest = 0;
-  for (int b = 0; b < a.B; ++b) {
-    fit = fit && a.tab.nnew[b] <= a.bb;
-    longest = a.tab.nnew[b] > longest ? a.tab.nnew[b] : longest;
-  }
-  // Positions per block: where no new token is pruned, so many that two
-  // workgroups per compute unit share the tokens (8 sequences x 8 kv heads x 40
-  // tokens: 12.4 us with blocks of 16, 16.2 with blocks of 64).
-  int bt = kPage;
-  if (fit)
-    while (bt > 16 && (int64_t)units * ((longest + bt / 2 - 1) / (bt / 2)) <= 512) bt /= 2;
-  int most = 0;       // blocks of one unit
-  int64_t total = 0;  // blocks of all
-  for (int b = 0; b < a.B; ++b) {
-    const int org = a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
-    const int n = a.tab.nnew[b] ? (a.tab.len[b] + a.tab.nnew[b] - org + bt - 1) / bt : 0;
-    most = n > most ? n : most;
-    total += (int64_t)n * 2 * a.Hkv;
-  }
-  // Long appends of binary16 rows go to the prefill kernel: its rotation on int8
-  // MFMA has twice the rate of float64's, but a workgroup first makes P's digits
-  // and takes 256 tokens at a time.  Measured (one unit = a kv head's keys or
-  // values, us, insert / prefill): 16 units x 1024 tokens 19 / 32, 128 x 256 31 /
-  // 33, 128 x 1024 105 / 67; 1024 units x 64 tokens 73 / 98, x 256 198 / 123.
-  const bool prefill = a.n_new >= kPrefillMinTokens && total > kPrefillMinBlocks &&
-                       sizeof(typename Fmt<F>::Elem) == 2;
-  // Blocks per workgroup: P's columns are loaded once for all of them (~2 us), so
-  // many blocks go up to 8 to a workgroup, as long as the GPU keeps 4 rounds of
-  // two workgroups per compute unit.  Where the units alone fill it, a few blocks
-  // stay together, so that the eviction needs no launch of its own.
-  int blocks = (int)(total / (256 * 2 * 4));
-  blocks = blocks < 1 ? 1 : blocks > 8 ? 8 : blocks;
-  if (a.max_evict > 0 && !fit && most <= 4 && units >= 256) blocks = most;
-  const int groups = (most + blocks - 1) / blocks;
-  const bool fused = !prefill && (fit || groups == 1);
-  if (a.max_evict > 0 && !fused) {
+  const AppendPlan pl = plan_append(a);
+  if (pl.kernel == kAppendNone) return hipSuccess;
+  if (a.max_evict > 0 && !pl.fused) {
     hipLaunchKernelGGL(evict_kernel<F>, dim3(units * a.max_evict), dim3(64), 0, a.stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  if (prefill) return launch_prefill(a);
-  if (most > 0) {
-    hipLaunchKernelGGL(insert_kernel<F>, dim3((int64_t)units * groups), dim3(64 * kInsWaves), 0,
-                       a.stream, a, groups, blocks, bt, fused && a.max_evict > 0);
-    return hipGetLastError();
-  }
-  return hipSuccess;
+  if (pl.kernel == kAppendPrefill) return launch_prefill(a);
+  hipLaunchKernelGGL(insert_kernel<F>, dim3((int64_t)units * pl.groups), dim3(64 * kInsWaves), 0,
+                     a.stream, a, pl.groups, pl.blocks, pl.bt, pl.fused && a.max_evict > 0);
+  return hipGetLastError();
 }
 
 hipError_t launch_compress(const CompressLaunch& a) {
@@ -608,3 +637,24 @@ hipError_t launch_compress(const CompressLaunch& a) {
 }
 
 }  // namespace swan
+
+extern "C" int32_t swan_append_kernel(int32_t dtype, int32_t batch, int32_t n_kv_heads,
+                                      int32_t buffer_tokens, const int32_t* seq_len_host,
+                                      int32_t n_new, const int32_t* n_new_host) {
+  if (!seq_len_host || batch < 1 || batch > SWAN_MAX_BATCH || n_new < 0) return -1;
+  if (n_new == 1) return swan::kAppendStep;
+  swan::CompressLaunch a = {};
+  a.dtype = dtype;
+  a.B = batch;
+  a.Hkv = n_kv_heads;
+  a.bb = buffer_tokens;
+  a.n_new = n_new;
+  for (int b = 0; b < batch; ++b) {
+    a.tab.len[b] = seq_len_host[b];
+    a.tab.nnew[b] = n_new_host ? n_new_host[b] : n_new;
+    const int evict = swan::evict_end(a.tab.len[b], a.tab.nnew[b], a.bb) -
+                      swan::evict_begin(a.tab.len[b], a.bb);
+    a.max_evict = evict > a.max_evict ? evict : a.max_evict;
+  }
+  return swan::plan_append(a).kernel;
+}

@@ -33,9 +33,12 @@ struct CompressLaunch {
 constexpr int kStepQG = 8;
 hipError_t launch_compress(const CompressLaunch& a);
 // prefill path (fp16, many tokens): int8 MFMA rotation, two lanes per token's top-k
-constexpr int kPrefillMinTokens = 256;
+constexpr int kPrefillMinTokens = 256;  // of the longest sequence, or
+constexpr int kPrefillMinMean = 160;    // on average, of the sequences that append
 constexpr int kPrefillMinBlocks = 512;  // of 64 positions, over all sequences, heads and roles
 hipError_t launch_prefill(const CompressLaunch& a);
+// what an append runs
+enum AppendKernel { kAppendNone, kAppendStep, kAppendInsert, kAppendPrefill };
 
 // run-time change of k: one launch per role, over the role's page arrays
 // (change_k.hip)
@@ -93,3 +96,9 @@ static_assert(kCalibPart * sizeof(double) >=
               "the reflectors, then the rotations, take the partials' place");
 
 }  // namespace swan
+
+// The AppendKernel of swan_compress_append with these arguments (-1: refused), for the
+// tests that are written for one of them; host arithmetic only.
+extern "C" int32_t swan_append_kernel(int32_t dtype, int32_t batch, int32_t n_kv_heads,
+                                      int32_t buffer_tokens, const int32_t* seq_len_host,
+                                      int32_t n_new, const int32_t* n_new_host);

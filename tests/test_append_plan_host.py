@@ -1,0 +1,41 @@
+"""Which kernel an append runs, from its lengths alone (host arithmetic): the rule looks at
+the tokens of the sequences, never at the stride of the rows they come in."""
+import ctypes
+
+import pytest
+
+swan = pytest.importorskip("paper_2511_18936_amd.swan")
+
+NONE, STEP, INSERT, PREFILL = range(4)
+F32, F16, E4M3 = swan.SWAN_F32, swan.SWAN_F16, swan.SWAN_F16_E4M3
+
+
+def append_kernel(dtype, heads, buffer, lens, n_new, per=None):
+    a = lambda v: None if v is None else (ctypes.c_int32 * len(v))(*v)
+    return swan.lib().swan_append_kernel(dtype, len(lens), heads, buffer, a(lens), n_new, a(per))
+
+
+@pytest.mark.parametrize("dtype", [F32, F16, E4M3])
+def test_rule(dtype):
+    long = INSERT if dtype == F32 else PREFILL
+    k = lambda *a: append_kernel(dtype, *a)
+    assert k(8, 64, [0] * 64, 1) == STEP and k(8, 64, [0] * 64, 0) == NONE
+    assert k(8, 64, [5] * 64, 256, [0] * 64) == NONE
+    # 1024 units: 64 tokens each, whatever the rows' stride; 160 and more
+    assert k(8, 0, [0] * 64, 64) == INSERT
+    assert k(8, 0, [0] * 64, 256, [64] * 64) == INSERT
+    assert k(8, 0, [0] * 64, 4096, [64] * 64) == INSERT
+    assert k(8, 0, [0] * 64, 159) == INSERT
+    assert k(8, 0, [0] * 64, 160) == long
+    assert k(8, 0, [1000] * 64, 4096, [160] * 64) == long
+    # sequences that append nothing do not count
+    assert k(8, 0, [0] * 64, 160, [160] * 32 + [0] * 32) == long
+    # 512 blocks of 64 positions are too few
+    assert k(8, 0, [0] * 16, 128) == INSERT
+    assert k(8, 0, [0] * 8, 256) == INSERT
+    assert k(8, 0, [0] * 8, 257) == long
+    assert k(8, 0, [0], 1009) == INSERT
+    # different lengths: by the mean, or by a long one
+    assert k(8, 0, [0] * 64, 200, [200, 40] * 32) == INSERT
+    assert k(8, 0, [0] * 64, 400, [400, 50] * 32) == long
+    assert k(8, 0, [0] * 64, 1000, ([1000] + [20] * 7) * 8) == long
