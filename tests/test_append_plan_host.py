@@ -39,3 +39,13 @@ def test_rule(dtype):
     assert k(8, 0, [0] * 64, 200, [200, 40] * 32) == INSERT
     assert k(8, 0, [0] * 64, 400, [400, 50] * 32) == long
     assert k(8, 0, [0] * 64, 1000, ([1000] + [20] * 7) * 8) == long
+
+
+@pytest.mark.parametrize("first,buffer", [(0, 0), (0, 33), (37, 16), (64, 128), (37, 0)])
+def test_lengths_of_the_prefill_tests(first, buffer):
+    """The batch that the prefill kernel's bit-exact tests append goes to that kernel."""
+    per = [(0, 1, 31, 32, 33, 64, 95, 256, 257, 288, 299, 300)[i % 12] for i in range(64)]
+    per = [300] + [max(n, 1 - first) if first == 0 else n for n in per[1:]]
+    for dtype in (F16, E4M3):
+        assert append_kernel(dtype, 2, buffer, [first] * 64, 300, per) == PREFILL
+    assert append_kernel(F16, 2, 0, [0] * 64, 260) == PREFILL

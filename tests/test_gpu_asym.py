@@ -34,7 +34,7 @@ def _dt(fmt):
 @pytest.mark.parametrize("fmt,L,b,kk,kv", [
     ("f16", 300, 16, 77, 51), ("f16", 200, 0, 13, 115), ("f16", 130, 16, 128, 1),
     ("f32", 300, 16, 64, 24), ("e4m3", 300, 16, 77, 51), ("e4m3", 129, 0, 96, 8),
-    # the prefill kernel's page copy: one LDS round for k_pad 88, two for 96
+    # k_pad 88 and 96, each way round
     ("f16", 300, 16, 88, 96), ("f16", 300, 16, 96, 88),
 ])
 def test_asym_compress_bit_exact(gpu_device, swan_mod, torch_mod, fmt, L, b, kk, kv):

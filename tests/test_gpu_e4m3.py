@@ -34,8 +34,8 @@ def _finite_fp16_rows():
 def test_e4m3_codes_of_every_fp16_value(gpu_device, swan_mod, torch_mod, single_appends):
     """P = identity, k = 128, b = 0: every token is pruned on arrival with all of its
     components kept, so the pages hold the E4M3 code of every input value: all finite
-    fp16 values, through the prefill kernel (one append) or the decode-step insert
-    (one token per append)."""
+    fp16 values, through the insert kernel (one append) or the decode-step kernel (one
+    token per append)."""
     torch = torch_mod
     _log(f"e4m3 codes of every fp16 value, single appends={single_appends}")
     X = _finite_fp16_rows()

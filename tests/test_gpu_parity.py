@@ -115,8 +115,8 @@ def _build(swan_mod, torch_mod, device, *, B, Hq, Hkv, L, b, k_active, dtype, ch
     ("f16", 1, 0, 48), ("f16", 130, 0, 48), ("f16", 200, 16, 1), ("f16", 200, 16, 128),
     ("f16", 333, 64, 13), ("f16", 64, 64, 48), ("f16", 40, 64, 48),
     ("f32", 300, 16, 64), ("f32", 129, 3, 5),
-    # pages that fit the prefill kernel's LDS copy (k_pad 88) and those that
-    # take two rounds (k_pad 96)
+    # k_pad 88 and 96 (these batches are small: the insert kernel's; the prefill
+    # kernel's cases are in test_gpu_prefill_units.py)
     ("f16", 300, 16, 88), ("f16", 300, 16, 81), ("f16", 300, 16, 89), ("f16", 129, 0, 96),
 ])
 def test_compress_prefill_bit_exact(gpu_device, swan_mod, torch_mod, dtype, L, b, k):
