@@ -191,9 +191,9 @@ __global__ __launch_bounds__(1024) void qr_kernel(CalibLaunch a) {
     for (int r = 0; r < kQrRows; ++r) xcol[0][kQrRows * g + r] = m[r];
   __syncthreads();
   dm = fmax(red[0], red[1]);
-  const bool graded = fmin(red[2], red[3]) < kGraded * dm;
-  if (tid == 0) a.graded[prob] = graded ? 1 : 0;
-  if (graded) return;  // uniform
+  const int graded = __builtin_amdgcn_readfirstlane(fmin(red[2], red[3]) < kGraded * dm ? 1 : 0);
+  if (tid == 0) a.graded[prob] = graded;
+  if (graded) return;
   const double tiny = 1e-60 * dm * dm;
   for (int k = 0; k < kD - 1; ++k) {
     const double* xc = xcol[k & 1];
@@ -280,7 +280,7 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 // Row r < kD: row r of Q^T G times Q, in place; row kD + r: row r of Q.  One wave
 // per row, lane l holds columns 2 l and 2 l + 1; grid (2 kD / 4, problems).
-// Graded: G stays as it is, Q = I.
+// Graded: no steps, so G stays as it is and Q = I.
 __global__ __launch_bounds__(256) void similar_kernel(CalibLaunch a) {
   const int lane = threadIdx.x & 63, prob = blockIdx.y;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -289,16 +289,13 @@ __global__ __launch_bounds__(256) void similar_kernel(CalibLaunch a) {
   const double* V = reflectors(a, prob);
   const double2* v = (const double2*)V + lane;
   double2 x = make_double2(r == 2 * lane ? 1.0 : 0.0, r == 2 * lane + 1 ? 1.0 : 0.0);
-  if (a.graded[prob]) {  // uniform
-    if (row >= kD) out[lane] = x;
-    return;
-  }
+  const int steps = a.graded[prob] ? 0 : kD - 1;
   if (row < kD) x = out[lane];
   constexpr int kAhead = 4;
   double2 next[kAhead];
 #pragma unroll
   for (int i = 0; i < kAhead; ++i) next[i] = v[i * kPairs];
-  for (int k0 = 0; k0 < kD - 1; k0 += kAhead) {
+  for (int k0 = 0; k0 < steps; k0 += kAhead) {
 #pragma unroll
     for (int i = 0; i < kAhead; ++i) {
       const int k = k0 + i;
