@@ -32,10 +32,10 @@
 // sits at positions 2 i and 2 i + 1, a round reads each 2 x 2 block of the
 // upper triangle once, rotates it from both sides and writes its elements where
 // the next round's positions put them, in a second buffer, all addresses fixed
-// for the whole solve: 1.03 us.  One head's 4096 rows: 1.45 ms (7 sweeps; 2.26
-// ms and 16 sweeps without the QR step), from 11.8 ms; a layer of 8 kv heads (16
-// problems of 5 k and 17 k rows, side by side instead of one after another): 2.16
-// ms (2.70 ms without the QR step), from 190 ms.
+// for the whole solve: 1.03 us.  One head's 4096 rows: 1.44 ms (7 sweeps; 2.26
+// ms and 16 sweeps without the QR step; 2.18 ms where the diagonal is graded), from
+// 11.8 ms; a layer of 8 kv heads (16 problems of 5 k and 17 k rows, side by side
+// instead of one after another): 2.2 ms (2.70 ms without the QR step), from 190 ms.
 #include <type_traits>
 
 #include "swan_cache_ops.h"
@@ -161,7 +161,10 @@ constexpr double kGraded = 1.0 / 64.0;
 // column (its own square norm among them, so that a step has two barriers) and
 // row k.  What is left below the diagonal by a skipped step stays in the matrix:
 // Q^T G is what is written, whatever its zeros.  2.7 us a step, the chain of its
-// two reductions (3.4 us with the matrix in LDS).
+// two reductions (3.4 us with the matrix in LDS): 0.35 ms a problem, which saves nine
+// sweeps of 0.13 ms on a spectrum like that of keys (16 to 7) and one on values over
+// output weights (11 to 10): alone those lose 0.2 ms by it, beside the keys' problems
+// of a layer, whose step takes that time anyway, they gain the sweep.
 __global__ __launch_bounds__(1024) void qr_kernel(CalibLaunch a) {
   __shared__ __attribute__((aligned(16))) double xcol[2][kD];
   __shared__ double part[kQrGroups][kD];

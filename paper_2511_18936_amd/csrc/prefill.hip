@@ -18,7 +18,7 @@
 // (counted per row) or of P (bounded per column).  Each
 // element is rounded to fp16 in two ways that must agree: both ends of its
 // error interval (widened by the float64 and float32 roundings) are rounded
-// through float32; about 7 elements in 10^4 disagree and get an exact
+// through float32; about 6 elements in 10^4 disagree and get an exact
 // certification in float64 (no fp16 rounding boundary within the bound of the
 // computed value), and the few that fail that are recomputed in float64 from
 // x and P.  Either way the stored value is the exact x_hat rounded once to
@@ -687,7 +687,7 @@ void prefill_kernel(CompressLaunch a, int units_per_wave) {
         // (another 2^-24) and that to fp16.  The margin covers the three
         // roundings, so the two bracket every value within E of x_hat; rounding
         // is monotone, so when they agree that is the fp16 rounding of x_hat.
-        // The elements whose ends disagree (about 1 in 2000) get the exact
+        // The elements whose ends disagree (about 6 in 10^4) get the exact
         // certification.
         const float dycv[4] = {dyc.x, dyc.y, dyc.z, dyc.w};
         uint32_t open[2][2];  // [T][v / 2]: nonzero halves where the ends disagree
