@@ -11,6 +11,8 @@
 //                  rotation x . P in float64 on MFMA, rounded once to the
 //                  storage type; tokens still inside the buffer go to their
 //                  ring slot, the others are pruned and packed at once
+//   few_kernel     the same for few tokens of many (sequence, kv head, role): one
+//                  wave per 8 tokens, float64 VALU
 //   step_kernel    a decode step: one workgroup of four waves per (sequence,
 //                  kv head, role), each wave a quarter of P's rows; the same
 //                  rounding, ring write or pruning, and the eviction.  In
@@ -399,6 +401,99 @@ void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict)
   }
 }
 
+// Few tokens of many units: one wave per kFewTokens of them, nothing shared, so that
+// every unit's chain of loads is in flight at once where insert_kernel takes several
+// rounds of workgroups of 8 waves.  Lane l rotates to dims 2 l and 2 l + 1, all 128
+// rows of P in batches of 32.  evict: the wave has all of its unit's new tokens and
+// first prunes and packs the vectors that leave the buffer (each lane reads the two
+// elements it overwrites later).
+constexpr int kFewTokens = 8;
+
+template <typename F>
+__global__ __launch_bounds__(64) void few_kernel(CompressLaunch a, int groups, bool evict) {
+  using T = typename Fmt<F>::Elem;
+  using St = Store<T>;
+  __shared__ __attribute__((aligned(16))) double xs[kD][kFewTokens];
+  const int lane = threadIdx.x;
+  int w = blockIdx.x;
+  const int grp = w % groups;
+  w /= groups;
+  const int role = w & 1;
+  w >>= 1;
+  const int h = w % a.Hkv;
+  const int b = w / a.Hkv;
+  const int t0 = grp * kFewTokens;
+  const int nnew = a.tab.nnew[b];
+  if (t0 >= nnew) return;
+  const int nt = nnew - t0 < kFewTokens ? nnew - t0 : kFewTokens;
+  const T* x = (const T*)(role ? a.v_new : a.k_new) +
+               (((int64_t)b * a.Hkv + h) * a.n_new + t0) * kD;
+#pragma unroll
+  for (int t = 0; t < kFewTokens; ++t) {
+    double v0 = 0.0, v1 = 0.0;
+    if (t < nt) {
+      v0 = (double)(float)x[(int64_t)t * kD + 2 * lane];
+      v1 = (double)(float)x[(int64_t)t * kD + 2 * lane + 1];
+    }
+    xs[2 * lane][t] = v0;
+    xs[2 * lane + 1][t] = v1;
+  }
+  const int len_old = a.tab.len[b], len_new = len_old + nnew;
+  const int k = a.tab.kact[role][b];
+  const int64_t pbytes = page_bytes_of(Fmt<F>::kValBytes, k);
+  char* pages = (char*)(role ? a.v_pages : a.k_pages) + a.tab.page_off[role][b] +
+                (int64_t)h * a.n_pages_cap * pbytes;
+  typename St::Bits* ring = (typename St::Bits*)(role ? a.v_ring : a.k_ring) +
+                            ((int64_t)b * a.Hkv + h) * a.bb * kD;
+  if (evict) {
+    const int p1 = evict_end(len_old, nnew, a.bb);
+    for (int p = evict_begin(len_old, a.bb); p < p1; ++p) {
+      const typename St::Bits* old = ring + (int64_t)(p % a.bb) * kD;
+      const typename St::Bits o0 = old[2 * lane], o1 = old[2 * lane + 1];
+      select_and_pack<F>(o0, o1, k, pages + (int64_t)(p / kPage) * pbytes, p % kPage, lane);
+    }
+  }
+  __syncthreads();  // xs
+  double acc0[kFewTokens], acc1[kFewTokens];
+  const float* Prole = role ? a.P_vo : a.P_qk;
+  if (!Prole) {  // values already in the rotated basis (P_VO absorbed into W_V)
+#pragma unroll
+    for (int t = 0; t < kFewTokens; ++t) {
+      acc0[t] = xs[2 * lane][t];
+      acc1[t] = xs[2 * lane + 1][t];
+    }
+  } else {
+    const float2* P = (const float2*)(Prole + (int64_t)h * kD * kD) + lane;
+#pragma unroll
+    for (int t = 0; t < kFewTokens; ++t) acc0[t] = acc1[t] = 0.0;
+#pragma unroll 32
+    for (int i = 0; i < kD; ++i) {
+      const float2 pr = P[i * (kD / 2)];
+      const double p0 = (double)pr.x, p1 = (double)pr.y;
+#pragma unroll
+      for (int t = 0; t < kFewTokens; ++t) {
+        const double xv = xs[i][t];
+        acc0[t] = fma(xv, p0, acc0[t]);
+        acc1[t] = fma(xv, p1, acc1[t]);
+      }
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < kFewTokens; ++t) {
+    if (t >= nt) break;
+    const typename St::Bits y0 = St::from_f64(acc0[t]);
+    const typename St::Bits y1 = St::from_f64(acc1[t]);
+    const int pos = len_old + t0 + t;
+    if (pos >= len_new - a.bb) {  // stays dense: ring slot pos % b
+      typename St::Bits* r = ring + (int64_t)(pos % a.bb) * kD;
+      r[2 * lane] = y0;
+      r[2 * lane + 1] = y1;
+    } else {  // pruned on arrival
+      select_and_pack<F>(y0, y1, k, pages + (int64_t)(pos / kPage) * pbytes, pos % kPage, lane);
+    }
+  }
+}
+
 // A decode step's append, one new token per sequence: one workgroup of four
 // waves per (sequence, kv head, role).  Wave s rotates with rows 32 s .. 32 s
 // + 31 of P, its 32 row loads issued together, so the rotation costs one
@@ -518,9 +613,23 @@ struct AppendPlan {
   int kernel;      // kAppend...
   int bt;          // positions per block
   int blocks;      // ... per workgroup of insert_kernel
-  int groups;      // workgroups per (sequence, kv head, role) of insert_kernel
-  bool fused;      // insert_kernel evicts; else an eviction launch goes first
+  int groups;      // workgroups per (sequence, kv head, role) of insert or few_kernel
+  bool fused;      // that kernel evicts; else an eviction launch goes first
 };
+
+// Blocks of an append of at most n tokens per unit from which few_kernel is faster than
+// insert_kernel; fit: no new token is pruned, evict: some leave the buffer.  Measured
+// (us, insert / few, units x tokens): binary16, fit, 1024 x 2 15.4 / 16.4, 1536 x 2
+// 21.7 / 19.8, 1536 x 8 22.3 / 23.9, 2048 x 8 28.8 / 25.8, 4096 x 2 54 / 36; evicting
+// 2048 x 2 32 / 23, x 8 36 / 33; pruned on arrival 512 x 2 13.5 / 16.8, 1024 x 2 24 /
+// 18, x 8 22.7 / 25.4, 2048 x 8 42 / 32, x 16 59 / 50.  float32: fit 768 x 2 13.5 / 15.0,
+// 1024 x 2 16.5 / 15.5, x 8 16.8 / 16.6; evicting 1024 x 4 20.6 / 22.7, 1536 x 4 29 / 28.5,
+// 2048 x 8 45 / 39; pruned 512 x 2 18.5 / 17.2, 1024 x 8 30 / 27, 2048 x 2 63 / 24.
+static int few_from(bool f32, bool fit, bool evict, int n) {
+  if (fit) return !f32 ? 1000 + 100 * n : evict ? 600 + 130 * n : 1000;
+  if (n <= kFewTokens) return f32 ? 300 + 60 * n : 500 + 100 * n;
+  return f32 ? (evict ? 1200 : 700) : (evict ? 1500 : 1000);  // the eviction in a launch
+}
 
 static AppendPlan plan_append(const CompressLaunch& a) {
   AppendPlan pl = {kAppendNone, kPage, 1, 0, false};
@@ -542,13 +651,26 @@ static AppendPlan plan_append(const CompressLaunch& a) {
       pl.bt /= 2;
   int most = 0;       // blocks of one unit
   int64_t total = 0;  // blocks of all
+  int64_t waves = 0;  // few_kernel's for all
   for (int b = 0; b < a.B; ++b) {
     const int org = a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
     const int n = a.tab.nnew[b] ? (a.tab.len[b] + a.tab.nnew[b] - org + pl.bt - 1) / pl.bt : 0;
     most = n > most ? n : most;
     total += (int64_t)n * 2 * a.Hkv;
+    waves += (int64_t)((a.tab.nnew[b] + kFewTokens - 1) / kFewTokens) * 2 * a.Hkv;
   }
   if (most == 0) return pl;
+  // Few tokens of many units.  A wave of few_kernel takes under half the time of a
+  // block of 64 that is pruned, more than half of a short one that fits the buffer
+  // (4096 units x 16 tokens, two waves each: pruned 112 us on insert_kernel, 85 on
+  // few_kernel, x 24, three waves, 114 / 117; dense, 16: 55 / 70).
+  if (waves <= (fit ? 1 : 2) * total &&
+      total >= few_from(a.dtype == SWAN_F32, fit, a.max_evict > 0, longest)) {
+    pl.kernel = kAppendFew;
+    pl.groups = (longest + kFewTokens - 1) / kFewTokens;
+    pl.fused = pl.groups == 1;
+    return pl;
+  }
   // Long appends of binary16 rows go to the prefill kernel: its rotation on int8
   // MFMA has twice the rate of float64's, but a workgroup first makes P's digits
   // and takes 256 tokens at a time.  Measured (one unit = a kv head's keys or
@@ -625,6 +747,11 @@ static hipError_t launch_compress_t(const CompressLaunch& a) {
     if (e != hipSuccess) return e;
   }
   if (pl.kernel == kAppendPrefill) return launch_prefill(a);
+  if (pl.kernel == kAppendFew) {
+    hipLaunchKernelGGL(few_kernel<F>, dim3((int64_t)units * pl.groups), dim3(64), 0, a.stream, a,
+                       pl.groups, pl.fused && a.max_evict > 0);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(insert_kernel<F>, dim3((int64_t)units * pl.groups), dim3(64 * kInsWaves), 0,
                      a.stream, a, pl.groups, pl.blocks, pl.bt, pl.fused && a.max_evict > 0);
   return hipGetLastError();

@@ -38,7 +38,7 @@ constexpr int kPrefillMinMean = 160;    // on average, of the sequences that app
 constexpr int kPrefillMinBlocks = 512;  // of 64 positions, over all sequences, heads and roles
 hipError_t launch_prefill(const CompressLaunch& a);
 // what an append runs
-enum AppendKernel { kAppendNone, kAppendStep, kAppendInsert, kAppendPrefill };
+enum AppendKernel { kAppendNone, kAppendStep, kAppendInsert, kAppendPrefill, kAppendFew };
 
 // run-time change of k: one launch per role, over the role's page arrays
 // (change_k.hip)

@@ -6,7 +6,7 @@ import pytest
 
 swan = pytest.importorskip("paper_2511_18936_amd.swan")
 
-NONE, STEP, INSERT, PREFILL = range(4)
+NONE, STEP, INSERT, PREFILL, FEW = range(5)
 F32, F16, E4M3 = swan.SWAN_F32, swan.SWAN_F16, swan.SWAN_F16_E4M3
 
 
@@ -49,3 +49,25 @@ def test_lengths_of_the_prefill_tests(first, buffer):
     for dtype in (F16, E4M3):
         assert append_kernel(dtype, 2, buffer, [first] * 64, 300, per) == PREFILL
     assert append_kernel(F16, 2, 0, [0] * 64, 260) == PREFILL
+
+
+@pytest.mark.parametrize("dtype,fresh,evicting,pruned", [
+    # units from which 2, 4 and 8 tokens of each go to the kernel for few tokens
+    (F16, (1200, 1400, 1800), (1200, 1400, 1800), (700, 900, 1300)),
+    (F32, (1000, 1000, 1000), (860, 1120, 1640), (420, 540, 780)),
+])
+def test_few_tokens_of_many_units(dtype, fresh, evicting, pruned):
+    for i, n in enumerate((2, 4, 8)):
+        for buffer, cached, at in ((64, 0, fresh[i]), (64, 1000, evicting[i]), (0, 960, pruned[i])):
+            heads = -(-at // 128)
+            for h in (heads - 1, heads):
+                want = FEW if 128 * h >= at else INSERT
+                assert append_kernel(dtype, h, buffer, [cached] * 64, n) == want, (n, buffer, h)
+    # more than 8: only where tokens are pruned, in blocks of 64 positions
+    assert append_kernel(dtype, 32, 64, [0] * 64, 9) == INSERT
+    assert append_kernel(dtype, 32, 0, [960] * 64, 16) == FEW
+    assert append_kernel(dtype, 32, 0, [960] * 64, 17) == INSERT
+    assert append_kernel(dtype, 32, 0, [1000] * 64, 32) == FEW  # over two pages
+    assert append_kernel(dtype, 32, 0, [1000] * 64, 33) == INSERT
+    # few sequences that append: as many blocks as those have
+    assert append_kernel(dtype, 32, 64, [0] * 64, 4, [4] * 4 + [0] * 60) == INSERT

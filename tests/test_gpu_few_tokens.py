@@ -1,0 +1,60 @@
+"""Few new tokens of very many (sequence, kv head, role), bit-exact against the oracle on
+sampled units: the kernel with one wave per 8 tokens, for tokens that fit the buffer, that
+make others leave it (in the same launch, or after an eviction launch) and that are pruned
+on arrival, up to two pages, with different lengths and none for some sequences."""
+import numpy as np
+import pytest
+
+import swan_inputs as si
+from oracle import swan_oracle as O
+from tests import swan_cases as C
+from tests.test_append_plan_host import FEW, append_kernel
+
+pytestmark = pytest.mark.gpu
+
+B, H = 64, 16  # 2048 units
+EDGES = [1, 7, 8, 9, 40, 63, 64, 77, 120, 121, 127, 128]
+
+
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("dtype,values", [("f16", "same"), ("f32", "same"), ("f16", "e4m3")])
+@pytest.mark.parametrize("first,n,b,ragged", [
+    (0, 2, 16, False), (0, 8, 16, True),           # fit, nothing leaves
+    (20, 5, 16, False), (64, 8, 8, True), (9, 7, 16, True),  # fit, the full or filling buffer leaves
+    (0, 3, 0, False), (62, 8, 0, True),            # no buffer; over a page's end
+    (20, 8, 3, False), (2, 6, 4, True),            # some leave, some are pruned
+    (0, 16, 0, False), (40, 32, 0, True), (30, 16, 5, False),  # several waves per unit
+])
+def test_few_tokens(gpu_device, swan_mod, torch_mod, dtype, values, first, n, b, ragged, given):
+    torch = torch_mod
+    np_dt = si.np_dtype(dtype)
+    per = [(n, n - 1, n, 1, n, 0)[i % 6] if ragged else n for i in range(B)]
+    # enough of them for every case
+    heads = 2 * H if ragged else H
+    assert append_kernel(swan_mod.dtype_code(C.torch_dtype(dtype), values), heads, b, [first] * B,
+                         n, per) == FEW
+    gen = torch.Generator(device=gpu_device).manual_seed(100 * n + first)
+    x = [torch.randn((B, heads, first + n, 128), device=gpu_device, generator=gen).to(
+        C.torch_dtype(dtype)) for _ in range(2)]
+    P = [np.stack([si.random_orthogonal(300 + 50 * r + h, 128) for h in range(4)]).astype(
+        np.float32) for r in range(2)]
+    tP = [torch.tensor(p, device=gpu_device).repeat(heads // 4, 1, 1) for p in P]
+    if given:
+        tP[1], P[1] = None, np.stack([np.eye(128)] * 4)
+    ks = [EDGES[i % len(EDGES)] for i in range(B)]
+    kv = [EDGES[(5 * i + 3) % len(EDGES)] for i in range(B)]
+    cache = swan_mod.SwanCache(B, heads, heads, b, first + n, ks, C.torch_dtype(dtype), gpu_device,
+                               sparse_values=values, k_value=kv)
+    if first:
+        cache.append(x[0][:, :, :first].contiguous(), x[1][:, :, :first].contiguous(), *tP)
+    cache.append(x[0][:, :, first:].contiguous(), x[1][:, :, first:].contiguous(), *tP,
+                 n_new_per_seq=per)
+    for i in range(24):
+        bi, h = (11 * i) % B, (7 * i + i // 4) % heads
+        L = first + per[bi]
+        if L == 0:
+            continue
+        K, V = (t[bi, h, :L].cpu().numpy() for t in x)
+        oc = O.compress_block(K, V, P[0][h % 4], P[1][h % 4], b, ks[bi], np_dt,
+                              values="e4m3" if values == "e4m3" else "t", k_value=kv[bi])
+        C.compare_unit(cache, oc, bi, h, L, np_dt, values=values)
