@@ -10,20 +10,25 @@
 
 namespace swan {
 
+template <typename T>
+__device__ __forceinline__ T rounded(double y) {
+  if constexpr (sizeof(T) == 2) return __builtin_bit_cast(T, f64_to_f16_bits_fast(y));
+  else return (T)y;
+}
+
 // One wave per (sequence, position) and `heads` of its heads.  base^(-2j/128) is
 // computed once per wave, the sine and cosine once per position, for all of its
-// heads.  E = 2: two heads at a time, lane l of a half wave holds the pairs
-// (2 l, 2 l + 64), (2 l + 1, 2 l + 65) of its head's row (4-byte accesses for
-// binary16).  E = 1: one head at a time, lane l holds the pair (l, l + 64).
+// heads.  Two heads at a time, lane l of a half wave holds the pairs (2 l, 2 l + 64),
+// (2 l + 1, 2 l + 65) of its head's row (4-byte accesses for binary16).
 //
-// What bounds it: many rows, memory; few, the chain of the float64 pow and sincos
-// (~300 instructions, twice that for E = 2).  32 heads x 1999 positions, binary16:
-// 46 us with these computed for every row, 14.9 us now; 8 heads: 13.9, 8.2 us; 16 x 32
-// heads x 8192: 2.55, 0.63 ms.
-template <typename T, int E>
+// What bounds it: memory.  32 heads x 1999 positions, binary16: 46 us with pow and
+// sincos for every row, 14.9 us now; 8 heads: 13.9, 8.2 us; 16 x 32 heads x 8192:
+// 2.55, 0.63 ms.
+template <typename T>
 __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int chunks) {
+  constexpr int E = 2;
   const int lane = threadIdx.x & 63;
-  const int l = E == 2 ? lane & 31 : lane, first = E == 2 ? lane >> 5 : 0;
+  const int l = lane & 31, first = lane >> 5;
   const int wpb = blockDim.x >> 6;
   const int64_t waves = (int64_t)gridDim.x * wpb;
   const int64_t items = (int64_t)a.B * a.n * chunks;
@@ -51,14 +56,8 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int 
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const double x0 = (double)(float)lo.v[e], x1 = (double)(float)hi.v[e];
-        const double y0 = x0 * c[e] - x1 * s[e], y1 = x1 * c[e] + x0 * s[e];
-        if constexpr (sizeof(T) == 2) {
-          p.v[e] = __builtin_bit_cast(T, f64_to_f16_bits_fast(y0));
-          q.v[e] = __builtin_bit_cast(T, f64_to_f16_bits_fast(y1));
-        } else {
-          p.v[e] = (T)y0;
-          q.v[e] = (T)y1;
-        }
+        p.v[e] = rounded<T>(x0 * c[e] - x1 * s[e]);
+        q.v[e] = rounded<T>(x1 * c[e] + x0 * s[e]);
       }
       *(Vec*)((T*)a.y + off) = p;
       *(Vec*)((T*)a.y + off + kD / 2) = q;
@@ -66,18 +65,47 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int 
   }
 }
 
+// Few rows: lane l holds the pair (l, l + 64) of one head after another, half the chain
+// of a lane with two pairs.  Grid (positions, chunks of heads, sequences).
+//
+// What bounds it: latency, the float64 pow and sincos (~300 instructions) after the
+// launch; so the first row is loaded before them and the grid numbers the items.  With
+// 64-bit divisions for that and the loads after the chain, float32 rows took 3.3 us
+// for 8 heads x 1 position and 5.9 for 32 x 100; now 2.7 and 4.3.
+template <typename T>
+__global__ __launch_bounds__(64) void rope_few_kernel(RopeLaunch a, int heads) {
+  const int l = threadIdx.x, i = blockIdx.x, b = blockIdx.z;
+  const int h0 = blockIdx.y * heads, h1 = min(a.H, h0 + heads);
+  int64_t off = (((int64_t)b * a.H + h0) * a.n + i) * kD + l;
+  T lo = ((const T*)a.x)[off], hi = ((const T*)a.x)[off + kD / 2];
+  double s, c;
+  sincos(((double)a.pos0[b] + (double)i) * pow(a.base, -(2.0 * l) / kD), &s, &c);
+#pragma unroll 1
+  for (int h = h0; h < h1; ++h) {
+    const int64_t next = off + (h + 1 < h1 ? (int64_t)a.n * kD : 0);
+    const double x0 = (double)(float)lo, x1 = (double)(float)hi;
+    if (h + 1 < h1) {
+      lo = ((const T*)a.x)[next];
+      hi = ((const T*)a.x)[next + kD / 2];
+    }
+    ((T*)a.y)[off] = rounded<T>(x0 * c - x1 * s);
+    ((T*)a.y)[off + kD / 2] = rounded<T>(x1 * c + x0 * s);
+    off = next;
+  }
+}
+
 template <typename T>
 static hipError_t launch_rope_t(const RopeLaunch& a) {
   // Up to 4096 waves (4 per SIMD), so that pow and sincos are shared by as many
   // rows as the GPU's size allows.  Few rows (a decode step, or a few thousand
-  // positions of few heads): E = 1, the shorter chain, one wave per workgroup; more
+  // positions of few heads): the shorter chain, one wave per workgroup; more
   // rows: two heads at a time, few positions splitting their heads.
   const int64_t rows = (int64_t)a.B * a.n;
   if (rows * a.H <= 4 * 4096) {
     const int heads = (int)((rows * a.H + 4095) / 4096);  // 1 to 4
     const int chunks = (a.H + heads - 1) / heads;
-    hipLaunchKernelGGL((rope_kernel<T, 1>), dim3((unsigned)(rows * chunks)), dim3(64), 0, a.stream,
-                       a, heads, chunks);
+    hipLaunchKernelGGL(rope_few_kernel<T>, dim3(a.n, chunks, a.B), dim3(64), 0, a.stream, a,
+                       heads);
     return hipGetLastError();
   }
   const int64_t most = (a.H + 1) / 2;
@@ -87,7 +115,7 @@ static hipError_t launch_rope_t(const RopeLaunch& a) {
   const int chunks = (a.H + heads - 1) / heads;
   const int64_t items = rows * chunks;
   const dim3 grid((unsigned)((items < 4096 ? items + 3 : 4096) / 4));
-  hipLaunchKernelGGL((rope_kernel<T, 2>), grid, dim3(256), 0, a.stream, a, heads, chunks);
+  hipLaunchKernelGGL(rope_kernel<T>, grid, dim3(256), 0, a.stream, a, heads, chunks);
   return hipGetLastError();
 }
 
