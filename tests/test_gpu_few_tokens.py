@@ -58,3 +58,24 @@ def test_few_tokens(gpu_device, swan_mod, torch_mod, dtype, values, first, n, b,
         oc = O.compress_block(K, V, P[0][h % 4], P[1][h % 4], b, ks[bi], np_dt,
                               values="e4m3" if values == "e4m3" else "t", k_value=kv[bi])
         C.compare_unit(cache, oc, bi, h, L, np_dt, values=values)
+
+
+def test_time_of_uneven_groups(gpu_device, swan_mod, torch_mod):
+    """8 blocks of every unit and one block more, in two groups of workgroups: the time of
+    the blocks, whatever processors their groups fall to (512 of 1024 tokens took 0.91 of
+    the time when the long groups shared half of them)."""
+    torch = torch_mod
+    heads, first, us = 32, 1000, {}
+    P = torch.eye(128, device=gpu_device).expand(heads, 128, 128).contiguous()
+    for n in (512, 1024):
+        cache = swan_mod.SwanCache(B, heads, heads, 0, first + n, [48] * B, torch.float32, gpu_device)
+        x = torch.randn((B, heads, n, 128), device=gpu_device)
+        for _ in range(4):
+            cache.seq_len = [first] * B
+            e = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+            e[0].record()
+            cache.append(x, x, P, P)
+            e[1].record()
+            torch.cuda.synchronize()
+            us[n] = min(us.get(n, 1e9), e[0].elapsed_time(e[1]))
+    assert us[512] <= 0.7 * us[1024], us
