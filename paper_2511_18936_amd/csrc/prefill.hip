@@ -404,15 +404,17 @@ void prefill_kernel(CompressLaunch a, int units_per_wave) {
   // grid: (b, h, role, group of units)
   // Workgroups go to the 8 XCDs round-robin by id, so XCD id % 8 gets the
   // (head, role) pairs u = xcd, xcd + 8, ...: its L2 then holds 1/8 of the P
-  // matrices instead of all of them.  Pairs are padded to a multiple of 8.
-  const int xcd = blockIdx.x % kXcds;
-  int w = blockIdx.x / kXcds;
+  // matrices instead of all of them.  Where the pairs are no multiple of 8, all of
+  // them alternate (with pairs padded to one, 2 kv heads used half of the XCDs: 256
+  // units x 160 tokens 53 us, 31 now).
+  const int pairs = 2 * a.Hkv, across = pairs % kXcds ? pairs : kXcds;
+  const int first = blockIdx.x % across;
+  int w = blockIdx.x / across;
   const int ngrp = a.prefill_groups;
   const int grp = w % ngrp;
   w /= ngrp;
   const int b = w % a.B;
-  const int u = xcd + kXcds * (w / a.B);  // (head, role) pair
-  if (u >= 2 * a.Hkv) return;
+  const int u = first + across * (w / a.B);  // (head, role) pair
   const int h = u >> 1;
   const int role = u & 1;
   const int len_old = a.tab.len[b];
@@ -834,7 +836,6 @@ static hipError_t launch_prefill_f(const CompressLaunch& a, dim3 grid, int upw) 
 
 hipError_t launch_prefill(const CompressLaunch& in) {
   CompressLaunch a = in;
-  const int pairs = (2 * a.Hkv + kXcds - 1) / kXcds * kXcds;  // (head, role), padded
   int64_t total = 0;  // units of all sequences, heads and roles
   int most = 0;       // of one sequence's head and role
   for (int b = 0; b < a.B; ++b) {
@@ -846,7 +847,7 @@ hipError_t launch_prefill(const CompressLaunch& in) {
   if (most == 0) return hipSuccess;
   const int upw = units_per_wave(total);
   a.prefill_groups = (most + kPrefillWaves * upw - 1) / (kPrefillWaves * upw);
-  const dim3 grid((int64_t)pairs * a.B * a.prefill_groups);
+  const dim3 grid((int64_t)2 * a.Hkv * a.B * a.prefill_groups);
   if (a.dtype == SWAN_F16_E4M3) return launch_prefill_f<E4M3V>(a, grid, upw);
   return launch_prefill_f<_Float16>(a, grid, upw);
 }

@@ -53,14 +53,16 @@ def test_prefill_units(gpu_device, swan_mod, torch_mod, first, b, hook, values):
     _check(cache, oc, Ls, values=values)
 
 
+@pytest.mark.parametrize("heads", [2, 3, 5])
 @pytest.mark.parametrize("old", [0, 37])
-def test_prefill_short_chunks(gpu_device, swan_mod, torch_mod, old):
-    """Chunks of 160 to 191 tokens of every sequence, the shortest that go to it."""
+def test_prefill_short_chunks(gpu_device, swan_mod, torch_mod, old, heads):
+    """Chunks of 160 to 191 tokens of every sequence, the shortest that go to it, of
+    (head, role) pairs that are no multiple of the XCDs."""
     Ls = [old + 160 + (7 * i) % 32 for i in range(B)]
     Ls[0] = old + 191
-    assert append_kernel(swan_mod.SWAN_F16, 2, 16, [old] * B, 191,
+    assert append_kernel(swan_mod.SWAN_F16, heads, 16, [old] * B, 191,
                          [L - old for L in Ls]) == PREFILL
-    cache, oc, *_ = _build(swan_mod, torch_mod, gpu_device, B=B, Hq=2, Hkv=2, L=Ls, b=16,
+    cache, oc, *_ = _build(swan_mod, torch_mod, gpu_device, B=B, Hq=heads, Hkv=heads, L=Ls, b=16,
                            k_active=[EDGES[i % len(EDGES)] for i in range(B)], dtype="f16",
                            chunks=[old, 191] if old else [191])
     _check(cache, oc, Ls)
