@@ -25,6 +25,10 @@
 // and orders by magnitude, then by lower index.  A binary search over the key
 // bits with wave ballots finds the k-th largest key; the selected entries are
 // then numbered in ascending dim order with mbcnt and written to the page.
+#include <limits.h>
+#include <math.h>
+#include <string.h>
+
 #include <type_traits>
 
 #include "swan_cache_ops.h"
@@ -237,6 +241,35 @@ __device__ __forceinline__ void select_rows(typename St::Bits* row, uint8_t* idx
   }
 }
 
+// The (sequence, kv head, role) and the group of a workgroup.  even: as many blocks in
+// every sequence, grid (units, groups); else grid (all workgroups), the sequence with the
+// most blocks first, its workgroups numbered together, group by group: tab.nsplit (what
+// a decode call keeps there, an append has no use for) holds each one's first number
+// times 64, plus the sequence.  So no number is left out and long and short do not alternate:
+// workgroups go to the 8 XCDs, and in each to 4 shader engines, round-robin, and where
+// every second one was short, or most had nothing to do, the others fell to the same few
+// processors (us, float32: 4096 units x 512 tokens, 8 blocks and 1 in two groups side by
+// side 3190, now 1750; 1024 units x 80, 64 and 16 in two groups 87, 61).
+__device__ __forceinline__ void place(const CompressLaunch& a, bool even, int lane, int& b,
+                                      int& h, int& role, int& grp) {
+  const unsigned per_seq = 2 * a.Hkv, id = blockIdx.x;
+  unsigned w;
+  if (even) {
+    b = (int)(id / per_seq);
+    grp = (int)blockIdx.y;
+    w = id - (unsigned)b * per_seq;
+  } else {
+    const bool upto = lane < a.B && ((uint32_t)a.tab.nsplit[lane] >> 6) <= id;
+    const uint32_t at = (uint32_t)a.tab.nsplit[__popcll(__ballot(upto)) - 1];
+    b = (int)(at & 63u);
+    w = id - (at >> 6);
+    grp = (int)(w / per_seq);
+    w -= (unsigned)grp * per_seq;
+  }
+  role = (int)(w & 1);
+  h = (int)(w >> 1);
+}
+
 // `blocks` blocks of `bt` positions per workgroup: 64 (pages), or, when no new
 // token is pruned (every sequence's fit its buffer), 16, 32 or 64.  evict: the
 // workgroup first prunes and packs the vectors that leave the buffer: all of its
@@ -252,7 +285,7 @@ __device__ __forceinline__ void select_rows(typename St::Bits* row, uint8_t* idx
 // of loads and barriers.
 template <typename F>
 __global__ __launch_bounds__(64 * kInsWaves) __attribute__((amdgpu_waves_per_eu(4)))
-void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict) {
+void insert_kernel(CompressLaunch a, bool even, int blocks, int bt, bool evict) {
   using T = typename Fmt<F>::Elem;
   using St = Store<T>;
   using Bits = typename St::Bits;
@@ -265,15 +298,8 @@ void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict)
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = lane & 15, g = lane >> 4;
-  // Group-major: workgroups go to the 8 XCDs round-robin, so with a unit's groups side
-  // by side and an even number of them, its short last group always fell to the same
-  // XCDs (4096 units x 512 tokens, float32, 8 blocks and 1: 3.19 ms, 1.75 now).
-  const int units = 2 * a.B * a.Hkv, grp = blockIdx.x / units;
-  int w = blockIdx.x % units;
-  const int role = w & 1;
-  w >>= 1;
-  const int h = w % a.Hkv;
-  const int b = w / a.Hkv;
+  int b, h, role, grp;
+  place(a, even, lane, b, h, role, grp);
   const int nnew = a.tab.nnew[b];
   if (nnew == 0) return;  // uniform
   const int len_old = a.tab.len[b], len_new = len_old + nnew;
@@ -281,6 +307,10 @@ void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict)
   const bool fits = nnew <= a.bb;
   const int org = fits ? len_old : len_old & ~(kPage - 1);
   const int nblk = (len_new - org + bt - 1) / bt;
+  if (!even && nblk > blocks) {  // the groups of a unit as long as each other
+    const int ng = (nblk + blocks - 1) / blocks;
+    blocks = (nblk + ng - 1) / ng;
+  }
   const int blk0 = grp * blocks, blk1 = blk0 + blocks < nblk ? blk0 + blocks : nblk;
   if (blk0 >= blk1) return;  // uniform
   const T* x = (const T*)(role ? a.v_new : a.k_new) + ((int64_t)b * a.Hkv + h) * a.n_new * kD;
@@ -412,17 +442,13 @@ void insert_kernel(CompressLaunch a, int groups, int blocks, int bt, bool evict)
 constexpr int kFewTokens = 8;
 
 template <typename F>
-__global__ __launch_bounds__(64) void few_kernel(CompressLaunch a, int groups, bool evict) {
+__global__ __launch_bounds__(64) void few_kernel(CompressLaunch a, bool even, bool evict) {
   using T = typename Fmt<F>::Elem;
   using St = Store<T>;
   __shared__ __attribute__((aligned(16))) double xs[kD][kFewTokens];
   const int lane = threadIdx.x;
-  const int units = 2 * a.B * a.Hkv, grp = blockIdx.x / units;  // as in insert_kernel
-  int w = blockIdx.x % units;
-  const int role = w & 1;
-  w >>= 1;
-  const int h = w % a.Hkv;
-  const int b = w / a.Hkv;
+  int b, h, role, grp;
+  place(a, even, lane, b, h, role, grp);
   const int t0 = grp * kFewTokens;
   const int nnew = a.tab.nnew[b];
   if (t0 >= nnew) return;
@@ -614,26 +640,130 @@ struct AppendPlan {
   int kernel;      // kAppend...
   int bt;          // positions per block
   int blocks;      // ... per workgroup of insert_kernel
-  int groups;      // workgroups per (sequence, kv head, role) of insert or few_kernel
+  int groups;      // workgroups of insert or few_kernel per (kv head, role): the most of
+                   // any sequence
+  int64_t wgs;     // ... of all
+  bool even;       // as many blocks in every sequence (and groups within a grid's limit);
+                   // else the sequences with the most blocks first:
+  uint32_t table[SWAN_MAX_BATCH];  // each one's first workgroup times 64, plus its number
   bool fused;      // that kernel evicts; else an eviction launch goes first
 };
 
-// Blocks of an append of at most n tokens per unit from which few_kernel is faster than
-// insert_kernel; fit: no new token is pruned, evict: some leave the buffer.  Measured
-// (us, insert / few, units x tokens): binary16, fit, 1024 x 2 15.4 / 16.4, 1536 x 2
-// 21.7 / 19.8, 1536 x 8 22.3 / 23.9, 2048 x 8 28.8 / 25.8, 4096 x 2 54 / 36; evicting
-// 2048 x 2 32 / 23, x 8 36 / 33; pruned on arrival 512 x 2 13.5 / 16.8, 1024 x 2 24 /
-// 18, x 8 22.7 / 25.4, 2048 x 8 42 / 32, x 16 59 / 50.  float32: fit 768 x 2 13.5 / 15.0,
-// 1024 x 2 16.5 / 15.5, x 8 16.8 / 16.6; evicting 1024 x 4 20.6 / 22.7, 1536 x 4 29 / 28.5,
-// 2048 x 8 45 / 39; pruned 512 x 2 18.5 / 17.2, 1024 x 8 30 / 27, 2048 x 2 63 / 24.
-static int few_from(bool f32, bool fit, bool evict, int n) {
-  if (fit) return !f32 ? 1000 + 100 * n : evict ? 600 + 130 * n : 1000;
-  if (n <= kFewTokens) return f32 ? 300 + 60 * n : 500 + 100 * n;
-  return f32 ? (evict ? 1200 : 700) : (evict ? 1500 : 1000);  // the eviction in a launch
+// What an append holds, over all sequences, kv heads and roles.
+struct AppendWork {
+  double blocks = 0, tiles = 0;     // insert_kernel's blocks and their tiles of 16 positions
+  double pruning = 0, uneven = 0;   // blocks with tokens pruned; with cut 128-byte lines of 8
+  double tokens = 0, waves = 0;     // few_kernel's waves
+  double pruned = 0, evicted = 0;   // new tokens pruned on arrival, tokens leaving the buffer
+  double evict_waves = 0;           // of an eviction launch
+};
+
+// Times of the two kernels in us, binary16 and float32: few_kernel's chain (per token
+// that a wave selects, and per other token) and a round of 1024 waves; insert_kernel's
+// and a round of 512 blocks, by what they do; the eviction in a launch of its own, and
+// per 1024 waves of it.  Fitted to both kernels' times at 256 to 4096 units x 2 to 48
+// tokens that fit the buffer, make others leave it, are pruned or both, from a page's
+// start and within it: 1400 shapes in each type.
+struct AppendCost {
+  double few, few_selected, few_token, wave, wave_selected;
+  double insert, block, tile, pruning, uneven, evicting, evicted;
+  double launch, launch_evicted;
+};
+constexpr AppendCost kCostF16 = {7.9, 0.99, 0.67, 6.42, 0.22, 3.15, 2.24,
+                                 4.13, 3.26, 0.66, 0.19, 0.19, 2.6, 0.68};
+constexpr AppendCost kCostF32 = {8.2, 1.15, 0.27, 6.21, 0.37, 4.34, 2.35,
+                                 4.12, 5.9, 2.17, 0.19, 0.39, 4.6, 1.02};
+
+// Whether few_kernel takes the append and not insert_kernel as `pl` has it: the smaller
+// of the times above.  No shape of the fit is slower by it than on the other kernel by
+// more than 15 % (those between two numbers of rounds), nine in ten not at all.  Some
+// (us, insert / few, units x tokens): binary16, fit, 1024 x 2 16 / 17, 2048 x 8 29 / 25,
+// x 16 30 / 41, 4096 x 2 56 / 37; evicting 2048 x 2 32 / 23, x 8 35 / 32; pruned 512 x 2
+// 13.6 / 16.7, 1152 x 16 29 / 38, 4096 x 2 85 / 37, x 20 118 / 107, x 24 115 / 121.
+// float32: fit 4096 x 8 56 / 36, x 16 59 / 64; evicting 4096 x 8 83 / 57, x 16 111 /
+// 129; pruned 4096 x 2 120 / 37, x 20 153 / 116, x 32 139 / 169.
+static bool few_is_faster(const AppendWork& w, const AppendPlan& pl, bool f32, bool one_wave) {
+  const AppendCost& c = f32 ? kCostF32 : kCostF16;
+  const double launch =
+      w.evict_waves > 0 ? c.launch + c.launch_evicted * w.evict_waves / 1024 : 0;
+  const double selected = (w.pruned + (one_wave ? w.evicted : 0)) / w.waves;  // per wave
+  const double others = w.tokens / w.waves - selected;
+  const double few = c.few + c.few_selected * selected + c.few_token * (others > 0 ? others : 0) +
+                     (c.wave + c.wave_selected * selected) * ceil(w.waves / 1024) +
+                     (one_wave ? 0 : launch);
+  const double a_block = c.block + (c.tile * w.tiles + c.pruning * w.pruning +
+                                    c.uneven * w.uneven) / w.blocks +
+                         (pl.fused && w.evicted > 0
+                              ? c.evicting + c.evicted * w.evicted / w.blocks : 0);
+  const double rounds = w.blocks / pl.wgs * ceil((double)pl.wgs / 512);
+  const double insert = c.insert + a_block * (rounds + w.blocks / 512) / 2 +
+                        (pl.fused ? 0 : launch);
+  return 1.02 * few < insert;
 }
 
+// First position of a sequence's blocks: anywhere where no new token is pruned.
+static int origin(const CompressLaunch& a, int b) {
+  return a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
+}
+
+// nblk: blocks of a unit of each sequence
+static AppendWork append_work(const CompressLaunch& a, const int32_t* nblk) {
+  AppendWork w;
+  for (int b = 0; b < a.B; ++b) {
+    const int len = a.tab.len[b], nnew = a.tab.nnew[b], org = origin(a, b);
+    if (nnew == 0) continue;
+    w.blocks += nblk[b];
+    // blocks are multiples of 16 positions from org on
+    w.tiles += (len + nnew - org + 15) / 16 - (len - org) / 16;
+    w.tokens += nnew;
+    w.waves += (nnew + kFewTokens - 1) / kFewTokens;
+    const int evict = evict_end(len, nnew, a.bb) - evict_begin(len, a.bb);
+    w.evicted += evict > 0 ? evict : 0;
+    if (nnew <= a.bb) continue;
+    const int end = len + nnew - a.bb;  // of the pruned positions
+    w.pruned += nnew - a.bb;
+    w.pruning += nblk[b];
+    const int cut = (len % 8 != 0) + (end % 8 != 0);
+    w.uneven += cut < nblk[b] ? cut : nblk[b];
+  }
+  w.evict_waves = (double)a.B * a.max_evict;
+  double* all[] = {&w.blocks, &w.tiles, &w.pruning, &w.uneven, &w.tokens,
+                   &w.waves, &w.pruned, &w.evicted, &w.evict_waves};
+  for (double* v : all) *v *= 2 * a.Hkv;
+  return w;
+}
+
+// The workgroups of pl, of nblk[b] blocks per unit, `blocks` per workgroup.
+static void place_workgroups(const CompressLaunch& a, const int32_t* nblk, int blocks,
+                             AppendPlan& pl) {
+  int most = 0, least = INT_MAX;
+  for (int b = 0; b < a.B; ++b) {
+    most = nblk[b] > most ? nblk[b] : most;
+    least = nblk[b] < least ? nblk[b] : least;
+  }
+  pl.groups = (most + blocks - 1) / blocks;
+  pl.wgs = (int64_t)a.B * pl.groups * 2 * a.Hkv;
+  pl.even = least == most && pl.groups <= 65535;
+  if (pl.even) return;
+  int order[SWAN_MAX_BATCH];
+  for (int b = 0; b < a.B; ++b) {  // sorted in place, equal ones in their order
+    int at = b;
+    for (; at > 0 && nblk[order[at - 1]] < nblk[b]; --at) order[at] = order[at - 1];
+    order[at] = b;
+  }
+  int64_t wgs = 0;
+  for (int at = 0; at < a.B; ++at) {
+    pl.table[at] = (uint32_t)wgs << 6 | (uint32_t)order[at];
+    wgs += (int64_t)((nblk[order[at]] + blocks - 1) / blocks) * 2 * a.Hkv;
+  }
+  if (wgs <= UINT32_MAX >> 6) pl.wgs = wgs;
+  else pl.even = true;  // (a grid that some workgroups leave at once)
+}
+static_assert(SWAN_MAX_BATCH <= 64, "the table's 6 bits, a ballot's lanes");
+
 static AppendPlan plan_append(const CompressLaunch& a) {
-  AppendPlan pl = {kAppendNone, kPage, 1, 0, false};
+  AppendPlan pl;
+  pl.kernel = kAppendNone;
   const int units = a.B * a.Hkv * 2;
   bool fit = true;  // no new token is pruned
   int longest = 0, appending = 0;
@@ -644,47 +774,24 @@ static AppendPlan plan_append(const CompressLaunch& a) {
     tokens += a.tab.nnew[b];
     appending += a.tab.nnew[b] > 0;
   }
+  if (longest == 0) return pl;
   // Positions per block: where no new token is pruned, so many that two
   // workgroups per compute unit share the tokens (8 sequences x 8 kv heads x 40
   // tokens: 12.4 us with blocks of 16, 16.2 with blocks of 64).
+  int shift = 6;
   if (fit)
-    while (pl.bt > 16 && (int64_t)units * ((longest + pl.bt / 2 - 1) / (pl.bt / 2)) <= 512)
-      pl.bt /= 2;
-  int most = 0;       // blocks of one unit
+    while (shift > 4 && (int64_t)units * ((longest + (1 << (shift - 1)) - 1) >> (shift - 1)) <= 512)
+      --shift;
+  pl.bt = 1 << shift;
+  int32_t nblk[SWAN_MAX_BATCH];  // blocks of a unit of each sequence
+  int most = 0;
   int64_t total = 0;  // blocks of all
-  int64_t waves = 0;  // few_kernel's for all
   for (int b = 0; b < a.B; ++b) {
-    const int org = a.tab.nnew[b] <= a.bb ? a.tab.len[b] : a.tab.len[b] & ~(kPage - 1);
-    const int n = a.tab.nnew[b] ? (a.tab.len[b] + a.tab.nnew[b] - org + pl.bt - 1) / pl.bt : 0;
-    most = n > most ? n : most;
-    total += (int64_t)n * 2 * a.Hkv;
-    waves += (int64_t)((a.tab.nnew[b] + kFewTokens - 1) / kFewTokens) * 2 * a.Hkv;
+    const int nnew = a.tab.nnew[b];
+    nblk[b] = nnew ? (a.tab.len[b] + nnew - origin(a, b) + pl.bt - 1) >> shift : 0;
+    most = nblk[b] > most ? nblk[b] : most;
+    total += (int64_t)nblk[b] * 2 * a.Hkv;
   }
-  if (most == 0) return pl;
-  // Few tokens of many units.  A wave of few_kernel takes under half the time of a
-  // block of 64 that is pruned, more than half of a short one that fits the buffer
-  // (4096 units x 16 tokens, two waves each: pruned 112 us on insert_kernel, 85 on
-  // few_kernel, x 24, three waves, 114 / 117; dense, 16: 55 / 70).
-  if (waves <= (fit ? 1 : 2) * total &&
-      total >= few_from(a.dtype == SWAN_F32, fit, a.max_evict > 0, longest)) {
-    pl.kernel = kAppendFew;
-    pl.groups = (longest + kFewTokens - 1) / kFewTokens;
-    pl.fused = pl.groups == 1;
-    return pl;
-  }
-  // Long appends of binary16 rows go to the prefill kernel: its rotation on int8
-  // MFMA has twice the rate of float64's, but a workgroup first makes P's digits
-  // and takes 256 tokens at a time.  Measured (one unit = a kv head's keys or
-  // values, us, insert / prefill), all sequences with as many tokens: 16 units x
-  // 1024 tokens 19 / 32, 128 x 256 (512 blocks) 29 / 28, 256 x 64 14 / 20, x 160
-  // 46 / 28, x 1024 195 / 115, 1024 x 64 43 / 62, x 160 133 / 91, x 256 195 / 108;
-  // on 1000 cached tokens, 64 of them evicted, 1024 x 96 110 / 117, x 128 131 / 125,
-  // x 160 158 / 125.  Of different lengths (1024 units): 200 and 40 tokens in turn
-  // 180 / 100; 300 for one sequence in 8, else 20: 79 / 166; 1000 for one in 8, else
-  // 20: 471 / 306.  The lengths are the sequences' own, not the rows' stride (64
-  // tokens each in rows for 256: 54 / 74).
-  const bool many = longest >= kPrefillMinTokens || tokens >= (int64_t)kPrefillMinMean * appending;
-  const bool prefill = many && total > kPrefillMinBlocks && a.dtype != SWAN_F32;
   // Blocks per workgroup: P's columns are loaded once for all of them (~2 us), so
   // many blocks go up to 8 to a workgroup, as long as the GPU keeps 4 rounds of
   // two workgroups per compute unit.  Where the units alone fill it, a few blocks
@@ -695,10 +802,41 @@ static AppendPlan plan_append(const CompressLaunch& a) {
   int blocks = (int)(total / (256 * 2 * 4));
   blocks = blocks < 1 ? 1 : blocks > 8 ? 8 : blocks;
   if (a.max_evict > 0 && !fit && most <= 4 && units >= 256) blocks = most;
-  pl.kernel = prefill ? kAppendPrefill : kAppendInsert;
+  pl.kernel = kAppendInsert;
   pl.blocks = blocks;
-  pl.groups = (most + blocks - 1) / blocks;
-  pl.fused = !prefill && (fit || pl.groups == 1);
+  place_workgroups(a, nblk, blocks, pl);
+  pl.fused = fit || pl.groups == 1;
+  // few_kernel: in the range of its fit, where both were measured (at 256 units it was
+  // never the faster one), tokens on average
+  if (appending * a.Hkv * 2 >= 512 && tokens <= (int64_t)48 * appending &&
+      few_is_faster(append_work(a, nblk), pl, a.dtype == SWAN_F32, longest <= kFewTokens)) {
+    pl.kernel = kAppendFew;
+    pl.fused = longest <= kFewTokens;
+    for (int b = 0; b < a.B; ++b) nblk[b] = (a.tab.nnew[b] + kFewTokens - 1) / kFewTokens;
+    place_workgroups(a, nblk, 1, pl);
+    return pl;
+  }
+  // Long appends of binary16 rows go to the prefill kernel: its rotation on int8 MFMA
+  // has twice the rate of float64's, but a workgroup first makes P's digits and takes
+  // 256 tokens at a time, and its grid has the longest sequence's workgroups for every
+  // sequence.  Measured (one unit = a kv head's keys or values, us, insert / prefill),
+  // all sequences with as many tokens: 16 units x 1024 19 / 29, 128 x 256 (512 blocks)
+  // 31 / 29, 256 x 64 19 / 22, x 160 39 / 31, x 1024 207 / 115; 1024 x 96 87 / 77, x 128
+  // 109 / 82, x 160 138 / 105, x 256 207 / 117; on 1000 cached tokens, 64 of them evicted,
+  // 1024 x 96 114 / 117, x 128 139 / 126, x 160 167 / 133, 128 of them, x 128 138 / 152,
+  // x 160 177 / 160.  Of different lengths (1024 units; one long sequence in so many):
+  // 400 and 100 in 2 255 / 208; 256, 64 in 2 135 / 110, evicting 180 / 237; 700, 200 in 4
+  // 303 / 213; 300, 20 in 8 68 / 164; 1000, 20 in 8 138 / 299; 1000, 100 in 4 276 / 326;
+  // 2000, 100 in 8 295 / 370; 2000, 300 in 4 602 / 575; 4000, 100 in 8 479 / 441.  The
+  // lengths are the sequences' own, not the rows' stride (64 tokens each in rows for 256:
+  // 54 / 74).
+  const double mean = (double)tokens / appending;
+  const bool many = mean >= (longest >= kPrefillMinTokens ? kPrefillMinMeanLong : kPrefillMinMean);
+  const bool alike = longest <= 2.25 * mean || mean >= kPrefillAnyMean;
+  if (many && alike && total > kPrefillMinBlocks && a.dtype != SWAN_F32) {
+    pl.kernel = kAppendPrefill;
+    pl.fused = false;
+  }
   return pl;
 }
 
@@ -748,13 +886,21 @@ static hipError_t launch_compress_t(const CompressLaunch& a) {
     if (e != hipSuccess) return e;
   }
   if (pl.kernel == kAppendPrefill) return launch_prefill(a);
-  if (pl.kernel == kAppendFew) {
-    hipLaunchKernelGGL(few_kernel<F>, dim3((int64_t)units * pl.groups), dim3(64), 0, a.stream, a,
-                       pl.groups, pl.fused && a.max_evict > 0);
-    return hipGetLastError();
+  const bool evict = pl.fused && a.max_evict > 0;
+  auto launch = [&](dim3 grid, const CompressLaunch& l) {
+    if (pl.kernel == kAppendFew)
+      hipLaunchKernelGGL(few_kernel<F>, grid, dim3(64), 0, a.stream, l, pl.even, evict);
+    else
+      hipLaunchKernelGGL(insert_kernel<F>, grid, dim3(64 * kInsWaves), 0, a.stream, l, pl.even,
+                         pl.blocks, pl.bt, evict);
+  };
+  if (pl.even) {
+    launch(dim3(units, pl.groups), a);
+  } else {
+    CompressLaunch l = a;
+    memcpy(l.tab.nsplit, pl.table, sizeof(pl.table));
+    launch(dim3((unsigned)pl.wgs), l);
   }
-  hipLaunchKernelGGL(insert_kernel<F>, dim3((int64_t)units * pl.groups), dim3(64 * kInsWaves), 0,
-                     a.stream, a, pl.groups, pl.blocks, pl.bt, pl.fused && a.max_evict > 0);
   return hipGetLastError();
 }
 

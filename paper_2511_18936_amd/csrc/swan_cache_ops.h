@@ -33,8 +33,10 @@ struct CompressLaunch {
 constexpr int kStepQG = 8;
 hipError_t launch_compress(const CompressLaunch& a);
 // prefill path (fp16, many tokens): int8 MFMA rotation, two lanes per token's top-k
-constexpr int kPrefillMinTokens = 256;  // of the longest sequence, or
-constexpr int kPrefillMinMean = 160;    // on average, of the sequences that append
+constexpr int kPrefillMinMean = 160;      // tokens per sequence that appends, on average,
+constexpr int kPrefillMinMeanLong = 128;  // ... with one of
+constexpr int kPrefillMinTokens = 256;
+constexpr int kPrefillAnyMean = 512;      // ... from which lengths may differ as they like
 constexpr int kPrefillMinBlocks = 512;  // of 64 positions, over all sequences, heads and roles
 hipError_t launch_prefill(const CompressLaunch& a);
 // what an append runs

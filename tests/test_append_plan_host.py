@@ -35,10 +35,15 @@ def test_rule(dtype):
     assert k(8, 0, [0] * 8, 256) == INSERT
     assert k(8, 0, [0] * 8, 257) == long
     assert k(8, 0, [0], 1009) == INSERT
-    # different lengths: by the mean, or by a long one
+    # different lengths: by the mean, unless a few long ones make it
     assert k(8, 0, [0] * 64, 200, [200, 40] * 32) == INSERT
-    assert k(8, 0, [0] * 64, 400, [400, 50] * 32) == long
-    assert k(8, 0, [0] * 64, 1000, ([1000] + [20] * 7) * 8) == long
+    assert k(8, 0, [0] * 64, 256, [256, 64] * 32) == long
+    assert k(8, 0, [0] * 64, 400, [400, 100] * 32) == long
+    assert k(8, 0, [0] * 64, 700, ([700] + [200] * 3) * 16) == long
+    assert k(8, 0, [0] * 64, 4000, ([4000] + [100] * 7) * 8) == long
+    assert k(8, 0, [0] * 64, 300, ([300] + [20] * 7) * 8) == INSERT
+    assert k(8, 0, [0] * 64, 1000, ([1000] + [20] * 7) * 8) == INSERT
+    assert k(8, 0, [0] * 64, 2000, ([2000] + [100] * 7) * 8) == INSERT
 
 
 @pytest.mark.parametrize("first,buffer", [(0, 0), (0, 33), (37, 16), (64, 128), (37, 0)])
@@ -51,23 +56,28 @@ def test_lengths_of_the_prefill_tests(first, buffer):
     assert append_kernel(F16, 2, 0, [0] * 64, 260) == PREFILL
 
 
-@pytest.mark.parametrize("dtype,fresh,evicting,pruned", [
-    # units from which 2, 4 and 8 tokens of each go to the kernel for few tokens
-    (F16, (1200, 1400, 1800), (1200, 1400, 1800), (700, 900, 1300)),
-    (F32, (1000, 1000, 1000), (860, 1120, 1640), (420, 540, 780)),
+@pytest.mark.parametrize("dtype,buffer,cached,few,insert", [
+    # (units, tokens of each) that the kernel for few tokens takes, or that go by
+    (F16, 128, 0, [(2048, 2), (2048, 8), (4096, 8)], [(256, 2), (1024, 4), (2048, 16), (4096, 24)]),
+    (F16, 64, 1000, [(2048, 4), (4096, 8)], [(768, 4), (1024, 8), (4096, 12)]),
+    (F16, 0, 960, [(768, 2), (2048, 8), (4096, 20)], [(512, 8), (1152, 16), (4096, 32)]),
+    (F16, 0, 1000, [(1024, 12), (4096, 16), (4096, 32)], [(512, 24), (2048, 48)]),
+    (F32, 128, 0, [(2048, 4), (4096, 8)], [(640, 8), (1024, 16), (4096, 32)]),
+    (F32, 64, 1000, [(2048, 2), (4096, 8)], [(640, 4), (1024, 12), (4096, 16)]),
+    (F32, 0, 960, [(640, 3), (2048, 12), (4096, 20)], [(512, 8), (896, 16), (4096, 32)]),
+    (F32, 0, 1000, [(1280, 16), (4096, 32)], [(512, 16), (4096, 64)]),
 ])
-def test_few_tokens_of_many_units(dtype, fresh, evicting, pruned):
-    for i, n in enumerate((2, 4, 8)):
-        for buffer, cached, at in ((64, 0, fresh[i]), (64, 1000, evicting[i]), (0, 960, pruned[i])):
-            heads = -(-at // 128)
-            for h in (heads - 1, heads):
-                want = FEW if 128 * h >= at else INSERT
-                assert append_kernel(dtype, h, buffer, [cached] * 64, n) == want, (n, buffer, h)
-    # more than 8: only where tokens are pruned, in blocks of 64 positions
-    assert append_kernel(dtype, 32, 64, [0] * 64, 9) == INSERT
-    assert append_kernel(dtype, 32, 0, [960] * 64, 16) == FEW
-    assert append_kernel(dtype, 32, 0, [960] * 64, 17) == INSERT
-    assert append_kernel(dtype, 32, 0, [1000] * 64, 32) == FEW  # over two pages
-    assert append_kernel(dtype, 32, 0, [1000] * 64, 33) == INSERT
-    # few sequences that append: as many blocks as those have
-    assert append_kernel(dtype, 32, 64, [0] * 64, 4, [4] * 4 + [0] * 60) == INSERT
+def test_few_tokens_of_many_units(dtype, buffer, cached, few, insert):
+    """Sizes where one of the two kernels measured faster by a tenth or more."""
+    for sizes, want in ((few, FEW), (insert, INSERT)):
+        for units, n in sizes:
+            got = append_kernel(dtype, units // 128, buffer, [cached] * 64, n)
+            assert got == want, (units, n)
+
+
+def test_few_tokens_of_some_sequences():
+    """By the sequences that append, and what all of them append."""
+    assert append_kernel(F16, 32, 64, [0] * 64, 4, [4] * 64) == FEW
+    assert append_kernel(F16, 32, 64, [0] * 64, 4, [4] * 4 + [0] * 60) == INSERT
+    assert append_kernel(F16, 32, 0, [1000] * 64, 300, [300] + [2] * 63) == FEW
+    assert append_kernel(F16, 32, 0, [1000] * 64, 300, [300] + [60] * 63) == INSERT

@@ -8,7 +8,7 @@ import pytest
 import swan_inputs as si
 from oracle import swan_oracle as O
 from tests import swan_cases as C
-from tests.test_append_plan_host import FEW, append_kernel
+from tests.test_append_plan_host import FEW, INSERT, append_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +23,7 @@ EDGES = [1, 7, 8, 9, 40, 63, 64, 77, 120, 121, 127, 128]
     (20, 5, 16, False), (64, 8, 8, True), (9, 7, 16, True),  # fit, the full or filling buffer leaves
     (0, 3, 0, False), (62, 8, 0, True),            # no buffer; over a page's end
     (20, 8, 3, False), (2, 6, 4, True),            # some leave, some are pruned
-    (0, 16, 0, False), (40, 32, 0, True), (30, 16, 5, False),  # several waves per unit
+    (40, 16, 0, False), (40, 32, 0, True), (30, 16, 5, False),  # several waves per unit
 ])
 def test_few_tokens(gpu_device, swan_mod, torch_mod, dtype, values, first, n, b, ragged, given):
     torch = torch_mod
@@ -58,6 +58,37 @@ def test_few_tokens(gpu_device, swan_mod, torch_mod, dtype, values, first, n, b,
         oc = O.compress_block(K, V, P[0][h % 4], P[1][h % 4], b, ks[bi], np_dt,
                               values="e4m3" if values == "e4m3" else "t", k_value=kv[bi])
         C.compare_unit(cache, oc, bi, h, L, np_dt, values=values)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "f32"])
+@pytest.mark.parametrize("first,b", [(0, 0), (37, 16), (70, 200)])
+def test_sequences_of_other_lengths(gpu_device, swan_mod, torch_mod, dtype, first, b):
+    """The insert kernel for sequences with different numbers of blocks, and so many of
+    some that a workgroup takes several: every sequence's units, also those of none."""
+    torch = torch_mod
+    heads, np_dt = 16, si.np_dtype(dtype)
+    per = [(1, 700, 0, 64, 65, 40, 127, 1, 513, 3)[i % 10] for i in range(B - 4)] + [0, 900, 20, 0]
+    assert append_kernel(swan_mod.dtype_code(C.torch_dtype(dtype), "same"), heads, b, [first] * B,
+                         900, per) == INSERT
+    gen = torch.Generator(device=gpu_device).manual_seed(first)
+    x = [torch.randn((B, heads, first + 900, 128), device=gpu_device, generator=gen).to(
+        C.torch_dtype(dtype)) for _ in range(2)]
+    P = [np.stack([si.random_orthogonal(400 + 50 * r + h, 128) for h in range(heads)]).astype(
+        np.float32) for r in range(2)]
+    tP = [torch.tensor(p, device=gpu_device) for p in P]
+    ks = [EDGES[i % len(EDGES)] for i in range(B)]
+    cache = swan_mod.SwanCache(B, heads, heads, b, first + 900, ks, C.torch_dtype(dtype), gpu_device)
+    if first:
+        cache.append(x[0][:, :, :first].contiguous(), x[1][:, :, :first].contiguous(), *tP)
+    cache.append(x[0][:, :, first:].contiguous(), x[1][:, :, first:].contiguous(), *tP,
+                 n_new_per_seq=per)
+    for bi in list(range(12)) + list(range(B - 5, B)):
+        L, h = first + per[bi], (3 * bi) % heads
+        if L == 0:
+            continue
+        K, V = (t[bi, h, :L].cpu().numpy() for t in x)
+        oc = O.compress_block(K, V, P[0][h], P[1][h], b, ks[bi], np_dt)
+        C.compare_unit(cache, oc, bi, h, L, np_dt)
 
 
 def test_time_of_uneven_groups(gpu_device, swan_mod, torch_mod):
