@@ -157,8 +157,8 @@ class SwanAttentionLayer:
     def _prompt_rows(self, x):
         """project(x) without the queries: a prompt's attention is not part of this layer,
         and for 32 query and 8 KV heads its keys and values are a third of the projections.
-        A project() of a subclass or of the object itself is called as it is."""
-        if getattr(self.project, "__func__", None) is not SwanAttentionLayer.project:
+        Any other project() than this class's own is called as it is."""
+        if getattr(self.project, "__func__", None) is not _OWN_PROJECT:
             return self.project(x)[1:]
         nq, nkv = self.n_heads * HEAD_DIM, self.n_kv_heads * HEAD_DIM
         kv = x @ self.W_qkv[:, nq:]
@@ -176,3 +176,6 @@ class SwanAttentionLayer:
         B = x.shape[0]
         o_hat = self.cache.step(k, v, q[:, :, 0].contiguous(), self.P_qk, None)
         return o_hat.view(B, self.n_heads * HEAD_DIM) @ self.W_o_hat
+
+
+_OWN_PROJECT = SwanAttentionLayer.project  # also when the class's is replaced

@@ -15,8 +15,8 @@ def _rows(x):
     return ("q", x), ("k", x), ("v", x)
 
 
-@pytest.mark.parametrize("where", ["subclass", "object"])
-def test_a_prompt_goes_through_an_own_project(where):
+@pytest.mark.parametrize("where", ["subclass", "object", "class"])
+def test_a_prompt_goes_through_an_own_project(where, monkeypatch):
     """project() may be replaced (biases, normalised keys): a prompt's rows are its rows."""
     import torch
 
@@ -28,6 +28,8 @@ def test_a_prompt_goes_through_an_own_project(where):
         Own if where == "subclass" else SwanAttentionLayer)
     if where == "object":
         layer.project = _rows
+    if where == "class":
+        monkeypatch.setattr(SwanAttentionLayer, "project", lambda self, x: _rows(x))
     layer.n_heads = layer.n_kv_heads = 1
     layer.W_qkv = torch.zeros(4, 3 * 128)
     layer.P_qk, layer.cache = "P_qk", _Cache()
