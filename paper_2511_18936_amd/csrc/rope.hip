@@ -22,8 +22,7 @@ __device__ __forceinline__ T rounded(double y) {
 // (2 l + 1, 2 l + 65) of its head's row (4-byte accesses for binary16).
 //
 // What bounds it: memory.  32 heads x 1999 positions, binary16: 46 us with pow and
-// sincos for every row, 14.9 us now; 8 heads: 13.9, 8.2 us; 16 x 32 heads x 8192:
-// 2.55, 0.63 ms.
+// sincos for every row, 14.8 us now; 16 x 32 heads x 8192: 2.45, 0.62 ms.
 template <typename T>
 __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int chunks) {
   constexpr int E = 2;
@@ -71,7 +70,8 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int 
 // What bounds it: latency, the float64 pow and sincos (~300 instructions) after the
 // launch; so the first row is loaded before them and the grid numbers the items.  With
 // 64-bit divisions for that and the loads after the chain, float32 rows took 3.3 us
-// for 8 heads x 1 position and 5.9 for 32 x 100; now 2.7 and 4.3.
+// for 8 heads x 1 position and 5.9 for 32 x 100, now 2.7 and 4.3; 8 x 1999, binary16,
+// 8.2 and 6.1 (13.4 with pow and sincos for every row).
 template <typename T>
 __global__ __launch_bounds__(64) void rope_few_kernel(RopeLaunch a, int heads) {
   const int l = threadIdx.x, i = blockIdx.x, b = blockIdx.z;
