@@ -383,13 +383,21 @@ void insert_kernel(CompressLaunch a, bool even, int blocks, int bt, bool evict) 
         for (int v = 0; v < 4; ++v)
           acc[v] = (double)xs[(16 * T + 4 * v + g) * kXStride + 16 * wave + m];
       }
+      Bits y[4];
+      bool nan = false;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        Bits y;
-        if constexpr (sizeof(Bits) == 2) y = f64_to_f16_bits_fast(acc[v]);
-        else y = St::from_f64(acc[v]);
-        rows[(16 * T + 4 * v + g) * RS + 16 * wave + m] = y;
+        if constexpr (sizeof(Bits) == 2) y[v] = f64_to_f16_bits_fast(acc[v]);
+        else y[v] = St::from_f64(acc[v]);
+        nan |= acc[v] != acc[v];
       }
+      if constexpr (sizeof(Bits) == 2) {
+        if (nan)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) y[v] = one_nan(y[v]);
+      }
+#pragma unroll
+      for (int v = 0; v < 4; ++v) rows[(16 * T + 4 * v + g) * RS + 16 * wave + m] = y[v];
     }
     __syncthreads();
     // dense tokens to the ring: slot pos % b

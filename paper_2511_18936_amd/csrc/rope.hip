@@ -16,6 +16,12 @@ __device__ __forceinline__ T rounded(double y) {
   else return (T)y;
 }
 
+// y: rounded results of a pair with a NaN
+template <typename T>
+__device__ __forceinline__ void one_nan_of(T& y) {
+  if constexpr (sizeof(T) == 2) y = __builtin_bit_cast(T, one_nan(__builtin_bit_cast(uint16_t, y)));
+}
+
 // One wave per (sequence, position) and `heads` of its heads.  base^(-2j/128) is
 // computed once per wave, the sine and cosine once per position, for all of its
 // heads.  Two heads at a time, lane l of a half wave holds the pairs (2 l, 2 l + 64),
@@ -52,12 +58,20 @@ __global__ __launch_bounds__(256) void rope_kernel(RopeLaunch a, int heads, int 
       const Vec lo = *(const Vec*)((const T*)a.x + off);
       const Vec hi = *(const Vec*)((const T*)a.x + off + kD / 2);
       Vec p, q;
+      bool nan = false;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const double x0 = (double)(float)lo.v[e], x1 = (double)(float)hi.v[e];
         p.v[e] = rounded<T>(x0 * c[e] - x1 * s[e]);
         q.v[e] = rounded<T>(x1 * c[e] + x0 * s[e]);
+        nan |= __builtin_isunordered((float)lo.v[e], (float)hi.v[e]);
       }
+      if (nan)
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+          one_nan_of(p.v[e]);
+          one_nan_of(q.v[e]);
+        }
       *(Vec*)((T*)a.y + off) = p;
       *(Vec*)((T*)a.y + off + kD / 2) = q;
     }
@@ -88,8 +102,13 @@ __global__ __launch_bounds__(64) void rope_few_kernel(RopeLaunch a, int heads) {
       lo = ((const T*)a.x)[next];
       hi = ((const T*)a.x)[next + kD / 2];
     }
-    ((T*)a.y)[off] = rounded<T>(x0 * c - x1 * s);
-    ((T*)a.y)[off + kD / 2] = rounded<T>(x1 * c + x0 * s);
+    T p = rounded<T>(x0 * c - x1 * s), q = rounded<T>(x1 * c + x0 * s);
+    if (x0 != x0 || x1 != x1) {
+      one_nan_of(p);
+      one_nan_of(q);
+    }
+    ((T*)a.y)[off] = p;
+    ((T*)a.y)[off + kD / 2] = q;
     off = next;
   }
 }

@@ -91,6 +91,37 @@ def test_sequences_of_other_lengths(gpu_device, swan_mod, torch_mod, dtype, firs
         C.compare_unit(cache, oc, bi, h, L, np_dt)
 
 
+@pytest.mark.parametrize("given", [False, True])
+@pytest.mark.parametrize("buffer", [0, 5, 64])
+def test_not_numbers(gpu_device, swan_mod, torch_mod, buffer, given):
+    """Rows with infinities and NaNs of any bits: the bytes of an append of all tokens are
+    those of one token after another; RoPE gives one NaN, with either sign."""
+    torch = torch_mod
+    gen = torch.Generator(device=gpu_device).manual_seed(3)
+    x = torch.randn((2, 4, 24, 128), device=gpu_device, generator=gen).half()
+    bits = [0x7E00, 0xFE00, 0x7D01, 0x7FFF, 0x7C00, 0xFC00, 0xFD03]
+    rows = x.view(torch.int16)
+    for i, v in enumerate(b - 65536 if b > 32767 else b for b in bits):
+        rows[0, 0, i, 5 * i + 1] = v
+        rows[1, 2, i] = v
+        rows[1, 3, i + 8, 3] = v
+    P = torch.tensor(np.stack([si.random_orthogonal(70 + h, 128) for h in range(4)]),
+                     dtype=torch.float32, device=gpu_device)
+    caches = [swan_mod.SwanCache(2, 4, 4, buffer, 64, [40, 128], torch.float16, gpu_device)
+              for _ in range(2)]
+    assert append_kernel(swan_mod.SWAN_F16, 4, buffer, [0, 0], 24) == INSERT
+    caches[0].append(x, x, P, None if given else P)
+    for t in range(24):
+        one = x[:, :, t:t + 1].contiguous()
+        caches[1].append(one, one, P, None if given else P)
+    for a, b in zip(*([c.k_pages, c.v_pages, c.k_ring.view(torch.int16), c.v_ring.view(torch.int16)]
+                      for c in caches)):
+        assert torch.equal(a, b)
+    y = swan_mod.rope(x, [3, 1000], 10000.0)
+    nan = y.view(torch.int16)[y.isnan()] & 0x7FFF
+    assert nan.numel() and bool((nan == 0x7E00).all())
+
+
 def test_time_of_uneven_groups(gpu_device, swan_mod, torch_mod):
     """8 blocks of every unit and one block more, in two groups of workgroups: the time of
     the blocks, whatever processors their groups fall to (512 of 1024 tokens took 0.91 of
