@@ -8,7 +8,7 @@ import pytest
 import swan_inputs as si
 from oracle import swan_oracle as O
 from tests import swan_cases as C
-from tests.test_append_plan_host import FEW, INSERT, append_kernel
+from tests.test_append_plan_host import FEW, INSERT, PREFILL, append_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -91,6 +91,15 @@ def test_sequences_of_other_lengths(gpu_device, swan_mod, torch_mod, dtype, firs
         C.compare_unit(cache, oc, bi, h, L, np_dt)
 
 
+def _not_numbers(torch, x):
+    rows = x.view(torch.int16)
+    for i, v in enumerate((0x7E00, 0xFE00, 0x7D01, 0x7FFF, 0x7C00, 0xFC00, 0xFD03)):
+        v -= 65536 if v > 32767 else 0
+        rows[0, 0, i, 5 * i + 1] = v
+        rows[1, -2, i] = v
+        rows[1, -1, i + 8, 3] = v
+
+
 @pytest.mark.parametrize("given", [False, True])
 @pytest.mark.parametrize("buffer", [0, 5, 64])
 def test_not_numbers(gpu_device, swan_mod, torch_mod, buffer, given):
@@ -99,12 +108,7 @@ def test_not_numbers(gpu_device, swan_mod, torch_mod, buffer, given):
     torch = torch_mod
     gen = torch.Generator(device=gpu_device).manual_seed(3)
     x = torch.randn((2, 4, 24, 128), device=gpu_device, generator=gen).half()
-    bits = [0x7E00, 0xFE00, 0x7D01, 0x7FFF, 0x7C00, 0xFC00, 0xFD03]
-    rows = x.view(torch.int16)
-    for i, v in enumerate(b - 65536 if b > 32767 else b for b in bits):
-        rows[0, 0, i, 5 * i + 1] = v
-        rows[1, 2, i] = v
-        rows[1, 3, i + 8, 3] = v
+    _not_numbers(torch, x)
     P = torch.tensor(np.stack([si.random_orthogonal(70 + h, 128) for h in range(4)]),
                      dtype=torch.float32, device=gpu_device)
     caches = [swan_mod.SwanCache(2, 4, 4, buffer, 64, [40, 128], torch.float16, gpu_device)
@@ -120,6 +124,28 @@ def test_not_numbers(gpu_device, swan_mod, torch_mod, buffer, given):
     y = swan_mod.rope(x, [3, 1000], 10000.0)
     nan = y.view(torch.int16)[y.isnan()] & 0x7FFF
     assert nan.numel() and bool((nan == 0x7E00).all())
+
+
+@pytest.mark.parametrize("buffer", [0, 40])
+def test_not_numbers_of_a_prompt(gpu_device, swan_mod, torch_mod, buffer):
+    """The prefill kernel's bytes of such rows are the insert kernel's, sequence by sequence."""
+    torch = torch_mod
+    gen = torch.Generator(device=gpu_device).manual_seed(4)
+    x = torch.randn((B, 2, 300, 128), device=gpu_device, generator=gen).half()
+    _not_numbers(torch, x)
+    P = torch.tensor(np.stack([si.random_orthogonal(70 + h, 128) for h in range(2)]),
+                     dtype=torch.float32, device=gpu_device)
+    new = lambda n: swan_mod.SwanCache(n, 2, 2, buffer, 300, [40] * n, torch.float16, gpu_device)
+    assert append_kernel(swan_mod.SWAN_F16, 2, buffer, [0] * B, 300) == PREFILL
+    all_, one = new(B), new(1)
+    all_.append(x, x, P, P)
+    for i in (0, 1, 2):
+        one.seq_len = [0]
+        one.append(x[i:i + 1], x[i:i + 1], P, P)
+        for a, b in ((all_.k_pages, one.k_pages), (all_.v_pages, one.v_pages),
+                     (all_.k_ring.view(torch.int16), one.k_ring.view(torch.int16)),
+                     (all_.v_ring.view(torch.int16), one.v_ring.view(torch.int16))):
+            assert torch.equal(a.reshape(B, -1)[i], b.flatten()), i
 
 
 def test_time_of_uneven_groups(gpu_device, swan_mod, torch_mod):
